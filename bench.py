@@ -194,6 +194,12 @@ def group_size(d_h, num_cus, batch):
     return G
 
 
+def register_list(w, M, B, scorer):
+    """Whether the call runs on the register-list expansion (the library's rule):
+    32 hidden units per workgroup of four waves, W_hh slices in registers."""
+    return (scorer == 0 and M <= 64 and B <= 64 and w.d_h <= (512 if w.dtype == 1 else 256))
+
+
 def main():
     args = parse()
     world = int(os.environ.get("WORLD_SIZE", "1"))
@@ -321,6 +327,12 @@ def main():
     num_cus = torch.cuda.get_device_properties(0).multi_processor_count
     G = group_size(w.d_h, num_cus, wl.batch)
     head_fast = head is not None and head_on_expand(HEAD_RANK, G)
+    grid, waves = (8 * G * ((wl.batch + 7) // 8)) if G > 1 else wl.batch, 8
+    if register_list(w, wl.M, wl.B, SCORERS[args.scorer]):
+        # at most two workgroups per CU: more trees than groups take turns
+        G, waves = w.d_h // 32, 4
+        groups = min(wl.batch, 8 * (2 * (num_cus // 8) // G))
+        grid = 8 * G * ((groups + 7) // 8)
     if head is None or head_fast:
         plan.set_profiling(1)
         for i in range(ncalls):
@@ -378,8 +390,8 @@ def main():
             "expanded_nodes_per_tree_mean": float(np.mean(exp_tree)),
             "alg_expansions_per_tree_mean": float(np.mean(alg_nodes)),
             "us_per_pop": exp_us / wl.B,   # per tree: the trees of a call run side by side
-            "workgroups_per_tree": G, "grid": (8 * G * ((wl.batch + 7) // 8)) if G > 1 else wl.batch,
-            "waves_per_workgroup": 8, "num_cus": num_cus,
+            "workgroups_per_tree": G, "grid": grid,
+            "waves_per_workgroup": waves, "num_cus": num_cus,
             "stats_calls": ncalls,
         })
     trees = wl.batch * args.steps

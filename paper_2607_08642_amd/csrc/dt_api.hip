@@ -71,7 +71,7 @@ hipError_t scratch_address(int dev, void **ptr) {
 namespace dt {
 
 // Lay out the workspace of one dt_build_tree call; base == nullptr only sizes it.
-Workspace carve(const dt_plan *p, int batch, char *base) {
+Workspace carve(const dt_plan *p, int batch, char *base, bool general) {
   Workspace ws{};
   const int rows = batch * p->L;
   const ScanGeom g = scan_geom(rows, p->V, p->M);
@@ -82,8 +82,17 @@ Workspace carve(const dt_plan *p, int batch, char *base) {
     return ptr;
   };
   ws.ecap = ecap_for(p);
-  ws.states = at((size_t)batch * ws.ecap * p->d_h * sizeof(float));
-  ws.part = at(expand_part_bytes(p, batch));
+  ws.grow = !general && grow_fits(p, batch);
+  size_t states = (size_t)batch * ws.ecap * p->d_h * sizeof(float), part = expand_part_bytes(p, batch);
+  if (ws.grow) {
+    // (never less than the general layout, so that a call's size does not depend
+    // on which kernel takes it)
+    const size_t gs = grow_state_bytes(p, batch), gp = grow_part_bytes(p, batch);
+    states = states > gs ? states : gs;
+    part = part > gp ? part : gp;
+  }
+  ws.states = at(states);
+  ws.part = at(part);
   // per tree: barrier counters; then the member-slot counters of the launch
   // (two sets: a call makes up to two expansion launches)
   ws.bar = reinterpret_cast<int32_t *>(at((size_t)2 * (batch + kSlotRows) * kBarStride * sizeof(int32_t)));
@@ -287,6 +296,7 @@ dt_status dt_plan_create_from_model(dt_plan **plan, dt_model *model, int L, int 
   p->max_lds = (size_t)maxlds;
   p->frontier_w = o.frontier_width;
   p->spin_limit = o.debug_spin_limit;
+  p->grow_occ = M <= 64 && B <= 64 ? dt::grow_max_occ(p->wdt, d_h, L, B, ncu, nxcd) : 0;
   p->device = dev;
   *plan = p;
   return DT_OK;
@@ -443,10 +453,10 @@ static dt_status check_build_args(const dt_plan *plan, const void *logits, int b
 
 // The launches of one dt_build_tree call on a checked, large enough workspace.
 static dt_status build_tree_on(dt_plan *plan, const void *logits, int batch, const float *h0,
-                               float T, void *workspace, dt_tree *out, void *stream) {
+                               float T, void *workspace, dt_tree *out, void *stream, bool general = false) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   const float inv_tau = T > 0.0f ? 1.0f / T : 1.0f;
-  dt::Workspace ws = dt::carve(plan, batch, static_cast<char *>(workspace));
+  dt::Workspace ws = dt::carve(plan, batch, static_cast<char *>(workspace), general);
   const dt::ScanGeom g = dt::scan_geom(batch * plan->L, plan->V, plan->M);
   // profiling every n-th call: the events' own cost (a few us each) stays small.
   // Calls captured into a graph are neither profiled nor counted.
@@ -486,8 +496,12 @@ static dt_status build_tree_on(dt_plan *plan, const void *logits, int batch, con
     mode.stats = plan->stats;
     plan->stats_batch = batch;
   }
-  e = dt::launch_expand(plan, batch, h0, inv_tau, ws, out, s, prof ? ev[2] : nullptr,
-                        prof ? ev[3] : nullptr, mode);
+  if (ws.grow)
+    e = dt::launch_grow(plan, batch, h0, inv_tau, ws, out, s, prof ? ev[2] : nullptr, prof ? ev[3] : nullptr,
+                        mode.stats);
+  else
+    e = dt::launch_expand(plan, batch, h0, inv_tau, ws, out, s, prof ? ev[2] : nullptr,
+                          prof ? ev[3] : nullptr, mode);
   if (e != hipSuccess) return hip_fail(e, "expand launch");
   if (prof) plan->profiled_calls++;
   return DT_OK;
@@ -508,7 +522,10 @@ dt_status dt_build_tree_noalloc(dt_plan *plan, const void *logits, int batch, co
                                 float T, dt_tree *out, void *stream) {
   const dt_status st = check_build_args(plan, logits, batch, h0, T, out);
   if (st != DT_OK) return st;
-  const size_t need = dt::carve(plan, batch, nullptr).bytes;
+  // (a layout for the general kernel can still fit where the larger one does not)
+  size_t need = dt::carve(plan, batch, nullptr).bytes;
+  const bool general = need > kScratchBytes;
+  if (general) need = dt::carve(plan, batch, nullptr, true).bytes;
   if (need > kScratchBytes)
     return fail(DT_ERR_WORKSPACE,
                 "batch %d needs %zu bytes of workspace, more than the %zu-byte scratch of "
@@ -523,7 +540,7 @@ dt_status dt_build_tree_noalloc(dt_plan *plan, const void *logits, int batch, co
   void *ws = nullptr;
   e = scratch_address(dev, &ws);  // resolved when the plan was created: a table lookup
   if (e != hipSuccess) return hip_fail(e, "scratch address");
-  return build_tree_on(plan, logits, batch, h0, T, ws, out, stream);
+  return build_tree_on(plan, logits, batch, h0, T, ws, out, stream, general);
 }
 
 dt_status dt_scan_workspace_size(int rows, int V, int M, size_t *bytes) {
@@ -593,7 +610,7 @@ struct HeadFastWs {
 };
 static HeadFastWs carve_head_fast(const dt_plan *p, int batch, int rank, int G, char *base) {
   HeadFastWs h;
-  h.ws = dt::carve(p, batch, base);
+  h.ws = dt::carve(p, batch, base, true);
   size_t o = h.ws.bytes;
   h.a = base ? reinterpret_cast<float *>(base + o) : nullptr;
   o += dt::align_up((size_t)batch * p->L * rank * sizeof(float), 256);

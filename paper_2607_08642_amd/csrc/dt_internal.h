@@ -38,6 +38,8 @@ constexpr int kFoldBK = 64;
 constexpr int kExpThreads = 512;
 constexpr int kNodeCap = 1536;       // live nodes per tree kept in LDS
 constexpr int kChunkNodes = 16;      // nodes expanded together (shared weight pass)
+constexpr int kGrowThreads = 256;    // the register-list expansion (dt_grow.hip)
+constexpr int kGrowUnits = 32;       // its hidden units per workgroup
 constexpr int kBarStride = 64;       // ints per tree of barrier counters (own cache lines)
 constexpr int kMaxXcd = 8;           // XCDs with a member-slot counter each
 constexpr int kSlotStride = 32;      // ints per XCD's slot counter (its own 128-byte line)
@@ -112,6 +114,7 @@ struct dt_plan {
   const void *whh_t, *whh_rm;
   int num_cus;
   int num_xcd;              // XCDs of the device (workgroups are dealt to them round-robin)
+  int grow_occ;             // workgroups of the register-list expansion a CU can hold (0: not taken)
   size_t max_lds;           // LDS bytes a workgroup may allocate on the device
   int frontier_w;           // dt_options.frontier_width (0: the heap builder)
   int spin_limit;           // dt_options.debug_spin_limit (0: the default)
@@ -147,6 +150,7 @@ struct Workspace {
   float *menus;           // [batch][L][MP] corrected menus of the greedy chain (scorer
                           // DT_SCORER_STATIC)
   int ecap;
+  bool grow;              // the register-list expansion takes the call
   size_t bytes;
 };
 
@@ -155,7 +159,8 @@ size_t merge_lds_bytes(const ScanGeom &g);  // LDS of the per-row merge (<= kMer
 size_t scan_bytes(const ScanGeom &g);
 // carve the scan part of a workspace; returns bytes used
 size_t carve_scan(char *base, const ScanGeom &g, Workspace *ws);
-Workspace carve(const dt_plan *p, int batch, char *base);
+// (general: laid out for the general expansion kernel whatever the shape)
+Workspace carve(const dt_plan *p, int batch, char *base, bool general = false);
 
 // kernel launchers (return hipError_t of the launch)
 // Domino's head: a[row][r] = W_1^H H_row over the launch's rows, computed by
@@ -224,6 +229,15 @@ int expand_group_size(int d_h, int num_cus, int num_xcd, int batch, int M, int L
 int expand_group_size(const dt_plan *p, int batch);
 size_t expand_lds_bytes(int dh, int G, int M, int nchunks, int L, int rj = 0, int wbytes = 0);
 size_t expand_part_bytes(const dt_plan *p, int batch);
+// the register-list expansion: whether a call takes it, its groups of workgroups,
+// workspace and launch
+bool grow_fits(const dt_plan *p, int batch);
+int grow_max_occ(int wdt, int d_h, int L, int B, int num_cus, int num_xcd);
+int grow_groups(const dt_plan *p, int batch);
+size_t grow_state_bytes(const dt_plan *p, int batch);
+size_t grow_part_bytes(const dt_plan *p, int batch);
+hipError_t launch_grow(const dt_plan *p, int batch, const float *h0, float inv_tau, const Workspace &ws,
+                       const dt_tree *out, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int32_t *stats);
 hipError_t pack_weights(dt_model *m, const dt_gru *gru, const dt_head *head, hipStream_t s);
 
 }  // namespace dt

@@ -519,17 +519,19 @@ __device__ __attribute__((always_inline)) void merge_row_wave(
 }
 
 // The same merge spread over the NT / 64 waves of a workgroup (every thread
-// calls it): wave w merges lists 2w and 2w + 1, then the tree's levels meet in
-// LDS (xbuf: NT keys), one barrier each; the tails combine as in block_tail.
+// calls it): wave w merges its kWaveMergeLists / (NT / 64) lists in registers,
+// then the tree's levels meet in LDS (xbuf: NT keys), one barrier each; the
+// tails combine as in block_tail.
 template <bool DEV_SCOPE, int NT, bool SHIFT = false>
 __device__ __attribute__((always_inline)) void merge_row_tree(
     const uint64_t *lists, int nlists, int M, const float2 *tails, const int32_t *flags, float c,
     float inv_tau, uint64_t *xbuf, float2 *red, int32_t *cand, float *candv, float *tailR,
     int32_t *rflag, const float *vadd) {
   constexpr int W = NT / 64;
-  static_assert(2 * W >= kWaveMergeLists, "two lists per wave");
+  constexpr int LPW = kWaveMergeLists / W;  // lists per wave
+  static_assert(LPW >= 2 && LPW * W == kWaveMergeLists, "at least two lists per wave");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = 2 * wave;  // this wave's first list; the tree as in merge_row_wave
+  const int j = LPW * wave;  // this wave's first list; the tree as in merge_row_wave
   Tail t = tail_empty();
   int bad = 0;
   if (wave == 0 && lane < nlists) {
@@ -537,26 +539,34 @@ __device__ __attribute__((always_inline)) void merge_row_tree(
     t = Tail{tl.x, tl.y};
     bad = flags[lane];
   }
-  uint64_t v = 0ull;
-  if (j < nlists) {
-    const uint64_t a = lane < M ? lists[j * M + lane] : 0ull;
-    const bool desc = (wave & 1) == 0;
-    if (j + 1 < nlists) {
-      const uint64_t b = 63 - lane < M ? lists[(j + 1) * M + 63 - lane] : 0ull;
-      v = merge_halves(a, b, desc, t, c);
-    } else {
-      v = desc ? a : bitonic_clean64(a, false);
-    }
+  uint64_t k[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    const int pos = (i & 1) ? 63 - lane : lane;
+    k[i] = (j + i < nlists && pos < M) ? lists[(j + i) * M + pos] : 0ull;
   }
 #pragma unroll
-  for (int s = 2; s < 2 * W; s <<= 1) {
+  for (int s = 1; s < LPW; s <<= 1) {
+#pragma unroll
+    for (int i = 0; i < LPW; i += 2 * s) {
+      if (j + i >= nlists) break;
+      const bool desc = (((j + i) / (2 * s)) & 1) == 0;
+      if (j + i + s < nlists)
+        k[i] = merge_halves(k[i], k[i + s], desc, t, c);
+      else if (!desc)
+        k[i] = bitonic_clean64(k[i], false);  // a lone list, now the right operand
+    }
+  }
+  uint64_t v = k[0];
+#pragma unroll
+  for (int s = LPW; s < kWaveMergeLists; s <<= 1) {
     // right operands publish; a slot read at this level is never written at the next
     if (j < nlists && (j % (2 * s)) == s) xbuf[wave * 64 + lane] = v;
     __syncthreads();
     if (j < nlists && (j % (2 * s)) == 0) {
       const bool desc = ((j / (2 * s)) & 1) == 0;
       if (j + s < nlists)
-        v = merge_halves(v, xbuf[(wave + s / 2) * 64 + lane], desc, t, c);
+        v = merge_halves(v, xbuf[(wave + s / LPW) * 64 + lane], desc, t, c);
       else if (!desc)
         v = bitonic_clean64(v, false);
     }

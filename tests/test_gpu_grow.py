@@ -1,0 +1,68 @@
+"""The register-list expansion (menus and budgets of at most 64) at the edges of what it takes,
+against the oracle: sizes around its constants (64 slots, 64 entries, 16 nodes per chunk, 32 units
+per workgroup), more trees than resident groups, and exact score ties."""
+import numpy as np
+import pytest
+
+from gpu_util import DeviceWorkload, compare_tree
+from paper_2607_08642_amd import synth
+
+pytestmark = pytest.mark.gpu
+F, H = synth.DT_F32, synth.DT_BF16
+
+# name, batch, L, V, M, B, T, d_h, weights, k, h0, norm, logit scale and spikes
+CASES = [
+    ("one_member", 3, 4, 301, 8, 8, 1.0, 32, F, 0, True, 0, 2.0),
+    ("one_slot", 2, 6, 300, 1, 16, 0.7, 64, F, 0, False, 0, 2.0),
+    ("budget_one", 2, 3, 300, 64, 1, 1.0, 64, H, 0, True, 1, 2.0),
+    ("full_list", 2, 5, 900, 64, 64, 0.0, 128, F, 0, True, 0, 0.3),
+    ("full_list_bf16", 1, 4, 2000, 64, 64, 0.0, 256, H, 0, False, 1, 0.3),
+    ("odd_members", 2, 4, 500, 33, 33, 0.7, 96, H, 5, True, 0, 1.0),
+    ("odd_members_f32", 2, 4, 500, 63, 17, 1.3, 160, F, 0, True, 1, 1.0),
+    ("cut_menus", 2, 4, 700, 64, 48, 1.0, 256, F, 3, True, 0, 0.3),
+    ("uneven_members_bf16", 1, 4, 400, 40, 20, 1.0, 416, H, 0, True, 0, 1.0),
+    ("deepest", 1, 64, 200, 8, 64, 1.0, 64, F, 2, False, 0, 6.0),
+    ("trees_in_turn", 37, 3, 400, 16, 12, 0.7, 512, H, 0, True, 0, 1.0),
+    ("trees_in_turn_one_per_cu", 20, 3, 400, 16, 64, 0.7, 512, H, 0, False, 0, 0.5),
+]
+
+
+@pytest.mark.parametrize("c", CASES, ids=[c[0] for c in CASES])
+def test_edges(c):
+    name, batch, L, V, M, B, T, d_h, dt, k, h0, norm, scale = c
+    print(f"[grow] {name}", flush=True)
+    wl = synth.random_small(len(name) + B, batch=batch, L=L, V=V, M=M, B=B, T=T, d_e=48, d_h=d_h, dtype=dt,
+                            h0=h0, logit_scale=scale, spikes=3, spike=3.0 * scale, w_scale=1.0 / np.sqrt(d_h))
+    dw = DeviceWorkload(wl, max_children=k, norm_mode=norm)
+    got = dw.run()
+    again = dw.run()
+    for f in got:
+        np.testing.assert_array_equal(got[f], again[f], err_msg=f)
+    for t in sorted({0, batch // 2, batch - 1}):
+        compare_tree(wl, t, got, dw.kw, name=name)
+    dw.close()
+
+
+@pytest.mark.parametrize("B", [16, 64])
+def test_plateau_order(B):
+    """Certain tokens: a child's log-prob rounds to 0, so whole chains share one score, beside twins
+    that tie exactly.  The heap works such a plateau first in, first out."""
+    wl = synth.twin_tokens(synth.random_small(5, batch=2, L=8, V=257, M=32, B=B, T=1.0, d_e=32, d_h=64, dtype=F,
+                                              emb_std=0.05, logit_scale=1.0, spikes=1, spike=0.0))
+    x = wl.logits
+    top = x.max(axis=-1, keepdims=True)
+    x[:, ::2] = np.where(x[:, ::2] == top[:, ::2], x[:, ::2] + 40.0, x[:, ::2])  # twins share every second row
+    dw = DeviceWorkload(wl)
+    got = dw.run()
+    for t in range(wl.batch):
+        n = int(got["n_nodes"][t])
+        s, p = got["scores"][t][:n], got["parents"][t][:n]
+        assert n == B and (np.diff(s) <= 0).all() and (p < np.arange(n)).all()
+        # first in, first out: within one score, nodes are ordered by (level, parent's place)
+        level = np.array([0] * n)
+        for i in range(n):
+            level[i] = level[p[i]] + 1 if p[i] >= 0 and s[p[i]] == s[i] else 0
+        key = list(zip(-s.astype(np.float64), level, p))
+        assert key == sorted(key), key
+        compare_tree(wl, t, got, dw.kw, name="plateau")
+    dw.close()
