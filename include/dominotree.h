@@ -213,7 +213,7 @@ dt_status dt_workspace_size(const dt_plan *plan, int batch, size_t *bytes);
  * Launches on `stream` and returns without waiting; the call may be captured
  * into a HIP graph (it records no memset or copy nodes, only its two kernels,
  * whose arguments are fixed at capture).  For small batches several
- * workgroups (at most one per CU in total) build each tree together and wait
+ * workgroups (at most two per CU in total) build each tree together and wait
  * on one another; they rely on being resident at the same time, which holds on
  * a device that other work does not fill.  Each wait is bounded: a tree whose
  * workgroups could not meet carries DT_TREE_TIMEOUT.  A workspace must not be

@@ -499,7 +499,9 @@ struct Gates<float> {  // fp32 W_hh: 16x16x4 fp32 MFMA, k-groups of 16, two per 
 // ARMS compiles the ablation-arm modes in (nocorr, menu_in, menu_out, emit,
 // skip_merge); without it they are fixed off and cost nothing.
 // HEAD scores with Domino's own head (a different correction; no ablation arms).
-template <typename TW, int SDH, int SG, int SM, int SL, bool ARMS, bool HEAD = false>
+// FRONT compiles the frontier builder in: beside the heap builder it costs
+// registers, 1-4% of a call.
+template <typename TW, int SDH, int SG, int SM, int SL, bool ARMS, bool HEAD = false, bool FRONT = false>
 __global__ __launch_bounds__(NT) void expand_kernel(ExpArgs a) {
   if constexpr (!ARMS) {
     a.nocorr = 0;
@@ -508,6 +510,7 @@ __global__ __launch_bounds__(NT) void expand_kernel(ExpArgs a) {
     a.menu_in = nullptr;
     a.menu_out = nullptr;
   }
+  if constexpr (!FRONT) a.W = 0;
   if constexpr (SDH > 0) a.dh = SDH;
   if constexpr (SG > 0) a.G = SG;
   if constexpr (SM > 0) a.M = SM;
@@ -826,6 +829,31 @@ __global__ __launch_bounds__(NT) void expand_kernel(ExpArgs a) {
     }
     best = wave_min_f(best);
     if (lane == 0) scalf[S_CNT0 + wave] = best;
+  };
+
+  // place(id, rank) for each of the n listed nodes: how many of the listed nodes
+  // precede it by (score desc, depth asc, table order); same: counting only those
+  // of its own depth.  Eight lanes share a node.
+  auto rank_candidates = [&](const int16_t *lst, int n, bool same, auto place) {
+    for (int q0 = 0; q0 < n; q0 += NT / 8) {
+      const int q = q0 + (tid >> 3);
+      const int id = lst[q < n ? q : 0];
+      const float gi = ng[id];
+      const int di = ndepth[id];
+      int r = 0;
+#pragma unroll 4
+      for (int j = tid & 7; j < n; j += 8) {
+        const int k = lst[j];
+        const float gj = ng[k];
+        const int dj = ndepth[k];
+        const bool before = gj > gi || (gj == gi && (dj < di || (dj == di && k < id)));
+        r += before && (!same || dj == di);
+      }
+      r += __shfl_xor(r, 1);
+      r += __shfl_xor(r, 2);
+      r += __shfl_xor(r, 4);
+      if (q < n && (tid & 7) == 0) place(id, r);
+    }
   };
 
   int pb = 0;  // partial-buffer parity
@@ -1572,17 +1600,14 @@ __global__ __launch_bounds__(NT) void expand_kernel(ExpArgs a) {
       // (score desc, table order), become lanes.  The table is depth-ordered,
       // and a depth's row is complete once the cursor reaches it (every node of
       // the depth above has been passed), which is when the flags are used.
-      // Nodes the table dropped (below vB) rank below every node that can still
-      // be taken, so counting the table gives the ledger's rank.
-      const int nn = scal[S_NN];
-      for (int i = tid; i < nn; i += NT) {
-        const int di = ndepth[i];
-        const float gi = ng[i];
-        int r = 0;
-        for (int j = i - 1; j >= 0 && ndepth[j] == di && r < a.W; --j) r += ng[j] >= gi;
-        for (int j = i + 1; j < nn && ndepth[j] == di && r < a.W; ++j) r += ng[j] > gi;
-        ins[i] = (uint8_t)(r < a.W);
-      }
+      // Only candidates (score >= vB) can be taken, and a node ranked above one is
+      // one itself, so counting the candidate list gives the ledger's rank.
+      // (Walking the table's run of the depth took 20,000 cycles a step, and ranking
+      // the table for the emission 36,000: four fp32 trees at d_h = 256, M = B = 32,
+      // W = 8 took 177 us a call, 113 with the lists.)
+      const int cl_ = ranked ? clist_r ^ 1 : clist_r;
+      rank_candidates(cl_ ? elist2 : elist, ranked ? scal[S_NNEXT0 + npar] : scal[S_NCAND], true,
+                      [&](int id, int r) { ins[id] = (uint8_t)(r < a.W); });
       __syncthreads();
     }
     // Every wave takes the select step itself, with identical results: vB,
@@ -1716,32 +1741,19 @@ __global__ __launch_bounds__(NT) void expand_kernel(ExpArgs a) {
   if (a.W > 0) {
     // frontier builder: the ledger's global top B by (score desc, depth asc,
     // table order) -- a parent ranks before its children -- in that order
-    const float vB = scalf[S_VB];
-    for (int i = tid; i < nn; i += NT) {
-      const float gi = ng[i];
-      const int di = ndepth[i];
-      int r = B;
-      if (gi >= vB) {
-        r = 0;
-        for (int j = 0; j < nn && r < B; ++j) {
-          const float gj = ng[j];
-          r += (gj > gi) | ((gj == gi) & ((ndepth[j] < di) | ((ndepth[j] == di) & (j < i))));
-        }
-      }
-      newidx[i] = (int16_t)(r < B ? r : -1);
-      if (r < B) order[r] = (int16_t)i;
-    }
-    if (tid == 0) scal[S_NPOP] = 0;
+    // (the B best are candidates)
+    const int ncand = scal[S_NCAND];
+    const int16_t *lst = scal[S_CLIST] ? elist2 : elist;
+    rank_candidates(lst, ncand, false, [&](int id, int r) {
+      newidx[id] = (int16_t)(r < B ? r : -1);
+      if (r < B) order[r] = (int16_t)id;
+    });
     __syncthreads();
-    int sel = 0;  // selected nodes this thread holds: min(B, nodes >= vB) in all
-    for (int i = tid; i < nn; i += NT) {
-      if (newidx[i] >= 0) {
-        const int par = nparent[i];
-        ppi[i] = (int16_t)(par >= 0 ? newidx[par] : -1);
-        ++sel;
-      }
+    for (int q = tid; q < ncand; q += NT) {
+      const int id = lst[q], par = nparent[id];
+      if (newidx[id] >= 0) ppi[id] = (int16_t)(par >= 0 ? newidx[par] : -1);
     }
-    if (sel) atomicAdd(&scal[S_NPOP], sel);
+    if (tid == 0) scal[S_NPOP] = ncand < B ? ncand : B;
   } else if (wave == 0) {
     // the candidates (every node scoring >= vB) are listed, in any order
     const int ncand = scal[S_NCAND];
@@ -2004,12 +2016,23 @@ hipError_t launch_expand(const dt_plan *p, int batch, const float *h0, float inv
     else
       fn = p->wdt == DT_BF16 ? (const void *)expand_kernel<uint16_t, 0, 0, 0, 0, false, true>
                              : (const void *)expand_kernel<float, 0, 0, 0, 0, false, true>;
-  } else if (arms)
+  } else if (arms && a.W > 0)
+    fn = p->wdt == DT_BF16 ? (const void *)expand_kernel<uint16_t, 0, 0, 0, 0, true, false, true>
+                           : (const void *)expand_kernel<float, 0, 0, 0, 0, true, false, true>;
+  else if (arms)
     fn = p->wdt == DT_BF16 ? (const void *)expand_kernel<uint16_t, 0, 0, 0, 0, true>
                            : (const void *)expand_kernel<float, 0, 0, 0, 0, true>;
-  else if (p->wdt == DT_BF16 && a.dh == 512 && a.M == 64 && a.L == 16 && a.G == 16)
+  else if (a.W > 0) {
+    if (qwen && a.G == 16)
+      fn = (const void *)expand_kernel<uint16_t, 512, 16, 64, 16, false, false, true>;
+    else if (qwen && a.G == 8)
+      fn = (const void *)expand_kernel<uint16_t, 512, 8, 64, 16, false, false, true>;
+    else
+      fn = p->wdt == DT_BF16 ? (const void *)expand_kernel<uint16_t, 0, 0, 0, 0, false, false, true>
+                             : (const void *)expand_kernel<float, 0, 0, 0, 0, false, false, true>;
+  } else if (qwen && a.G == 16)  // (here and below: budgets over 64)
     fn = (const void *)expand_kernel<uint16_t, 512, 16, 64, 16, false>;
-  else if (p->wdt == DT_BF16 && a.dh == 512 && a.M == 64 && a.L == 16 && a.G == 8)
+  else if (qwen && a.G == 8)
     fn = (const void *)expand_kernel<uint16_t, 512, 8, 64, 16, false>;
   else if (p->wdt == DT_BF16)
     fn = (const void *)expand_kernel<uint16_t, 0, 0, 0, 0, false>;
