@@ -238,6 +238,25 @@ dt_status dt_build_tree(dt_plan *plan, const void *marginal_logits, int batch, c
 dt_status dt_build_tree_noalloc(dt_plan *plan, const void *marginal_logits, int batch,
                                 const float *h0, float T, dt_tree *out, void *stream);
 
+/* One-shot form: trees from raw weights without a model or plan.  Only the
+ * embedding rows of the calls' candidates are folded (batch L M rows instead of
+ * V), into the workspace; nothing is allocated or kept.
+ *   shapes, weights and options as dt_plan_create (the weights are read by the
+ *   call's kernels: keep them until the stream has passed it), the rest as
+ *   dt_build_tree.
+ * Takes what needs fewer rows than the vocabulary and fits the kernel that keeps
+ * its candidates in registers: batch L M < V, DT_SCORER_COND, frontier_width 0,
+ * M <= 64, B <= 64, at most 16 scan segments per row, d_h <= 512 (fp32: 256);
+ * DT_ERR_UNSUPPORTED otherwise (create a plan).  Launches on `stream` and returns
+ * without waiting.  dt_once_workspace_size gives the workspace (256-byte aligned). */
+dt_status dt_once_workspace_size(int V, int d_e, int d_h, int weights_dtype, int L, int M, int B,
+                                 int logits_dtype, int batch, const dt_options *opts, size_t *bytes);
+dt_status dt_build_tree_once(const void *emb, int V, int d_e, const dt_gru *gru, const dt_head *head,
+                             int weights_dtype, int L, int M, int B, int logits_dtype,
+                             const void *marginal_logits, int batch, const float *h0, float T,
+                             const dt_options *opts, void *workspace, size_t ws_bytes, dt_tree *out,
+                             void *stream);
+
 /* Release the plan's device memory and its reference to the model (NULL is
  * ignored). */
 void dt_plan_destroy(dt_plan *plan);

@@ -36,7 +36,8 @@ EXPORTS = ("dt_abi_version", "dt_status_string", "dt_last_error", "dt_plan_creat
            "dt_plan_stage_ms", "dt_scan_workspace_size", "dt_scan_topm", "dt_head_workspace_size",
            "dt_build_tree_head", "dt_build_tree_noalloc",
            "dt_plan_expand_stats", "dt_plan_set_adaptive_budget", "dt_model_create",
-           "dt_model_destroy", "dt_plan_create_from_model")
+           "dt_model_destroy", "dt_plan_create_from_model", "dt_once_workspace_size",
+           "dt_build_tree_once")
 STAGES = ("scan", "expand")
 
 
@@ -126,6 +127,11 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.dt_plan_expand_stats.argtypes = [vp, vp, vp, ci]
     lib.dt_build_tree_noalloc.restype = ci
     lib.dt_build_tree_noalloc.argtypes = [vp, vp, ci, vp, cf, ctypes.POINTER(dt_tree), vp]
+    lib.dt_once_workspace_size.restype = ci
+    lib.dt_once_workspace_size.argtypes = [ci] * 9 + [ctypes.POINTER(dt_options), ctypes.POINTER(sz)]
+    lib.dt_build_tree_once.restype = ci
+    lib.dt_build_tree_once.argtypes = [vp, ci, ci, ctypes.POINTER(dt_gru), ctypes.POINTER(dt_head)] + [ci] * 5 + \
+        [vp, ci, vp, cf, ctypes.POINTER(dt_options), vp, sz, ctypes.POINTER(dt_tree), vp]
     if lib.dt_abi_version() != ABI_VERSION:
         raise RuntimeError(f"ABI mismatch: library {lib.dt_abi_version()} vs binding {ABI_VERSION}")
     _lib = lib
@@ -385,12 +391,36 @@ class Plan:
 def build_tree(marginal_logits, emb, gru_weights, correction_head, L: int, M: int, B: int,
                T: float, h0=None, max_children: int = 0, norm_mode: int = DT_NORM_TAIL,
                pos_offset: int = 0, scorer: int = DT_SCORER_COND, frontier_width: int = 0) -> Tree:
-    """One-shot form of the paper's build_tree(...) -> tree (creates and drops a plan).
+    """One-shot form of the paper's build_tree(...) -> tree; returns when the trees are built.
 
+    Folds the candidates' embedding rows only where dt_build_tree_once takes the
+    shape; otherwise creates and drops a plan (the whole vocabulary folded).
     gru_weights = (w_ih, w_hh, b_ih, b_hh); correction_head = (w_c, b_c).
     """
+    import torch
     w_ih, w_hh, b_ih, b_hh = gru_weights
     w_c, b_c = correction_head
+    lib = load()
+    V, d_e = emb.shape
+    d_h, batch = w_hh.shape[1], marginal_logits.shape[0]
+    wdt, ldt = _dtype_code(emb), _dtype_code(marginal_logits)
+    opts = dt_options(max_children, norm_mode, pos_offset, scorer, frontier_width, 0)
+    n = ctypes.c_size_t()
+    if lib.dt_once_workspace_size(V, d_e, d_h, wdt, L, M, B, ldt, batch, ctypes.byref(opts),
+                                  ctypes.byref(n)) == 0:
+        stream = torch.cuda.current_stream()
+        default = torch.cuda.default_stream()
+        if stream != default:
+            stream.wait_stream(default)   # (weights just written there)
+        out = Tree.empty(batch, B, marginal_logits.device)
+        ws = torch.empty(n.value, dtype=torch.uint8, device=marginal_logits.device)
+        gru = dt_gru(_ptr(w_ih), _ptr(w_hh), _ptr(b_ih), _ptr(b_hh), d_e, d_h)
+        head = dt_head(_ptr(w_c), _ptr(b_c))
+        _check(lib.dt_build_tree_once(_ptr(emb), V, d_e, ctypes.byref(gru), ctypes.byref(head), wdt, L, M, B,
+                                      ldt, _ptr(marginal_logits), batch, _ptr(h0), T, ctypes.byref(opts),
+                                      ws.data_ptr(), n.value, ctypes.byref(out.as_c()), _stream(stream)))
+        stream.synchronize()
+        return out
     plan = Plan(emb, w_ih, w_hh, b_ih, b_hh, w_c, b_c, L=L, M=M, B=B,
                 logits_dtype=_dtype_code(marginal_logits), max_batch=marginal_logits.shape[0],
                 max_children=max_children, norm_mode=norm_mode, pos_offset=pos_offset,
@@ -398,7 +428,6 @@ def build_tree(marginal_logits, emb, gru_weights, correction_head, L: int, M: in
     try:
         return plan.build_tree(marginal_logits, T, h0)
     finally:
-        import torch
         torch.cuda.current_stream().synchronize()
         plan.close()
 

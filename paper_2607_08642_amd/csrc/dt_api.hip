@@ -154,23 +154,37 @@ static void model_release(dt_model *m) {
   delete m;
 }
 
-dt_status dt_model_create(dt_model **model, const void *emb, int V, int d_e, const dt_gru *gru,
-                          const dt_head *head, int weights_dtype) {
-  if (!model) return fail(DT_ERR_NULL, "model out-pointer is NULL");
-  *model = nullptr;
-  if (!emb || !gru || !head) return fail(DT_ERR_NULL, "emb, gru and head are required");
-  if (!gru->w_ih || !gru->w_hh || !head->w) return fail(DT_ERR_NULL, "w_ih, w_hh and head.w are required");
+// the sizes and dtypes of a model's tensors
+static dt_status check_model_shape(int V, int d_e, const dt_gru *gru, int weights_dtype) {
   if (!valid_dtype(weights_dtype)) return fail(DT_ERR_DTYPE, "dtype codes must be DT_F32 or DT_BF16");
   if (V < 1 || d_e < 1) return fail(DT_ERR_SHAPE, "sizes must be positive (V=%d d_e=%d)", V, d_e);
   if (gru->d_in != d_e) return fail(DT_ERR_SHAPE, "gru.d_in (%d) must equal d_e (%d)", gru->d_in, d_e);
   const int d_h = gru->d_h;
   if (d_e > dt::kMaxDe || d_h < 32 || d_h > dt::kMaxDh || d_h % 32 != 0)
     return fail(DT_ERR_UNSUPPORTED, "outside the envelope (d_e<=8192, 32<=d_h<=1024, d_h%%32==0)");
+  return DT_OK;
+}
+
+static dt_status check_model_align(const void *emb, const dt_gru *gru, const dt_head *head, int weights_dtype) {
   const size_t ws = dsize(weights_dtype);
   if (!aligned(emb, 16) || !aligned(gru->w_ih, ws) || !aligned(gru->w_hh, ws) ||
       !aligned(head->w, ws) || (gru->b_ih && !aligned(gru->b_ih, ws)) ||
       (gru->b_hh && !aligned(gru->b_hh, ws)) || (head->b && !aligned(head->b, ws)))
     return fail(DT_ERR_ALIGN, "emb must be 16-byte aligned, weights naturally aligned");
+  return DT_OK;
+}
+
+dt_status dt_model_create(dt_model **model, const void *emb, int V, int d_e, const dt_gru *gru,
+                          const dt_head *head, int weights_dtype) {
+  if (!model) return fail(DT_ERR_NULL, "model out-pointer is NULL");
+  *model = nullptr;
+  if (!emb || !gru || !head) return fail(DT_ERR_NULL, "emb, gru and head are required");
+  if (!gru->w_ih || !gru->w_hh || !head->w) return fail(DT_ERR_NULL, "w_ih, w_hh and head.w are required");
+  dt_status cst = check_model_shape(V, d_e, gru, weights_dtype);
+  if (cst == DT_OK) cst = check_model_align(emb, gru, head, weights_dtype);
+  if (cst != DT_OK) return cst;
+  const int d_h = gru->d_h;
+  const size_t ws = dsize(weights_dtype);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "device query");
@@ -217,13 +231,11 @@ dt_status dt_model_create(dt_model **model, const void *emb, int V, int d_e, con
 
 void dt_model_destroy(dt_model *model) { model_release(model); }
 
-dt_status dt_plan_create_from_model(dt_plan **plan, dt_model *model, int L, int M, int B,
-                                    int logits_dtype, int max_batch, const dt_options *opts) {
-  if (!plan) return fail(DT_ERR_NULL, "plan out-pointer is NULL");
-  *plan = nullptr;
-  if (!model) return fail(DT_ERR_NULL, "model is required");
+// A plan of one (L, M, B) shape over a model of the given sizes living on device
+// `model_dev` (which must be current), its tables and model still to be set.
+static dt_status plan_init(dt_plan *p, int V, int d_e, int d_h, int wdt, int model_dev, int L, int M, int B,
+                           int logits_dtype, int max_batch, const dt_options *opts) {
   if (!valid_dtype(logits_dtype)) return fail(DT_ERR_DTYPE, "dtype codes must be DT_F32 or DT_BF16");
-  const int V = model->V, d_h = model->d_h;
   if (L < 1 || M < 1 || B < 1 || max_batch < 1)
     return fail(DT_ERR_SHAPE, "sizes must be positive (L=%d M=%d B=%d max_batch=%d)", L, M, B, max_batch);
   if (M > V) return fail(DT_ERR_SHAPE, "M (%d) exceeds V (%d)", M, V);
@@ -239,8 +251,8 @@ dt_status dt_plan_create_from_model(dt_plan **plan, dt_model *model, int L, int 
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return hip_fail(e, "device query");
-  if (dev != model->device)
-    return fail(DT_ERR_SHAPE, "the model lives on device %d, the current device is %d", model->device, dev);
+  if (dev != model_dev)
+    return fail(DT_ERR_SHAPE, "the model lives on device %d, the current device is %d", model_dev, dev);
   if (nxcd < 1 || nxcd > dt::kMaxXcd)
     return fail(DT_ERR_UNSUPPORTED, "device reports %d XCDs; 1 to %d are supported", nxcd, dt::kMaxXcd);
   if (dt::merge_lds_bytes(dt::scan_geom(1, V, M)) > (size_t)dt::kMergeLdsMax)
@@ -260,25 +272,10 @@ dt_status dt_plan_create_from_model(dt_plan **plan, dt_model *model, int L, int 
     return fail(DT_ERR_UNSUPPORTED,
                 "expansion needs %zu bytes of LDS (d_h=%d, M=%d, max_batch=%d), device has %d",
                 lds_need, d_h, M, max_batch, maxlds);
-  void *scratch_ptr = nullptr;
-  e = scratch_address(dev, &scratch_ptr);  // once per device: dt_build_tree_noalloc's workspace
-  if (e != hipSuccess) return hip_fail(e, "scratch address");
-
-  dt_plan *p = new (std::nothrow) dt_plan();
-  if (!p) return fail(DT_ERR_HIP, "host allocation failed");
-  model->refs.fetch_add(1);
-  p->model = model;
   p->V = V;
-  p->d_e = model->d_e;
+  p->d_e = d_e;
   p->d_h = d_h;
-  p->wdt = model->wdt;
-  p->P_all = model->P_all;
-  p->U_all = model->U_all;
-  p->c_all = model->c_all;
-  p->b_ih = model->b_ih;
-  p->b_hh = model->b_hh;
-  p->whh_t = model->whh_t;
-  p->whh_rm = model->whh_rm;
+  p->wdt = wdt;
   p->L = L;
   p->M = M;
   p->B = B;
@@ -296,8 +293,36 @@ dt_status dt_plan_create_from_model(dt_plan **plan, dt_model *model, int L, int 
   p->max_lds = (size_t)maxlds;
   p->frontier_w = o.frontier_width;
   p->spin_limit = o.debug_spin_limit;
-  p->grow_occ = M <= 64 && B <= 64 ? dt::grow_max_occ(p->wdt, d_h, L, B, ncu, nxcd) : 0;
+  p->grow_occ = M <= 64 && B <= 64 ? dt::grow_max_occ(wdt, d_h, L, B, ncu, nxcd) : 0;
   p->device = dev;
+  return DT_OK;
+}
+
+dt_status dt_plan_create_from_model(dt_plan **plan, dt_model *model, int L, int M, int B,
+                                    int logits_dtype, int max_batch, const dt_options *opts) {
+  if (!plan) return fail(DT_ERR_NULL, "plan out-pointer is NULL");
+  *plan = nullptr;
+  if (!model) return fail(DT_ERR_NULL, "model is required");
+  dt_plan *p = new (std::nothrow) dt_plan();
+  if (!p) return fail(DT_ERR_HIP, "host allocation failed");
+  const dt_status st = plan_init(p, model->V, model->d_e, model->d_h, model->wdt, model->device, L, M, B,
+                                 logits_dtype, max_batch, opts);
+  void *scratch_ptr = nullptr;
+  hipError_t e = hipSuccess;
+  if (st == DT_OK) e = scratch_address(p->device, &scratch_ptr);  // once per device: dt_build_tree_noalloc's workspace
+  if (st != DT_OK || e != hipSuccess) {
+    delete p;
+    return st != DT_OK ? st : hip_fail(e, "scratch address");
+  }
+  model->refs.fetch_add(1);
+  p->model = model;
+  p->P_all = model->P_all;
+  p->U_all = model->U_all;
+  p->c_all = model->c_all;
+  p->b_ih = model->b_ih;
+  p->b_hh = model->b_hh;
+  p->whh_t = model->whh_t;
+  p->whh_rm = model->whh_rm;
   *plan = p;
   return DT_OK;
 }
@@ -541,6 +566,111 @@ dt_status dt_build_tree_noalloc(dt_plan *plan, const void *logits, int batch, co
   e = scratch_address(dev, &ws);  // resolved when the plan was created: a table lookup
   if (e != hipSuccess) return hip_fail(e, "scratch address");
   return build_tree_on(plan, logits, batch, h0, T, ws, out, stream, general);
+}
+
+// ---- one-shot calls --------------------------------------------------------------
+// Everything a call needs beside its inputs, in the workspace: the build's own part
+// and a model whose tables hold a row per candidate slot.
+struct OnceWs {
+  dt::Workspace ws;
+  dt_model m;  // (never shared: no references counted)
+  size_t bytes;
+};
+static void carve_once(const dt_plan *p, int batch, char *base, OnceWs *w) {
+  w->ws = dt::carve(p, batch, base);
+  size_t o = w->ws.bytes;
+  auto at = [&](size_t bytes) {
+    char *ptr = base ? base + o : nullptr;
+    o += dt::align_up(bytes, 256);
+    return ptr;
+  };
+  const size_t es = dsize(p->wdt), rows = (size_t)batch * p->L * p->M;
+  dt_model &m = w->m;
+  m.V = p->V;
+  m.d_e = p->d_e;
+  m.d_h = p->d_h;
+  m.wdt = p->wdt;
+  m.device = p->device;
+  m.nf = 4 * p->d_h;
+  m.nf_pad = (m.nf + dt::kFoldBN - 1) / dt::kFoldBN * dt::kFoldBN;
+  m.wfold = at((size_t)m.nf_pad * p->d_e * es);
+  m.b_ih = reinterpret_cast<float *>(at(sizeof(float) * 3 * p->d_h));
+  m.b_hh = reinterpret_cast<float *>(at(sizeof(float) * 3 * p->d_h));
+  m.b_c = reinterpret_cast<float *>(at(sizeof(float) * p->d_e));
+  m.whh_t = at((size_t)3 * p->d_h * p->d_h * es);
+  m.P_all = reinterpret_cast<float *>(at(rows * 3 * p->d_h * sizeof(float)));
+  m.U_all = reinterpret_cast<float *>(at(rows * p->d_h * sizeof(float)));
+  m.c_all = reinterpret_cast<float *>(at(rows * sizeof(float)));
+  w->bytes = o;
+}
+
+// The plan of a one-shot call; DT_ERR_UNSUPPORTED where folding the candidates is
+// no less work than folding the vocabulary (batch L M >= V), or the register-list
+// expansion does not take the shape.
+static dt_status once_plan(dt_plan *p, int V, int d_e, int d_h, int weights_dtype, int L, int M, int B,
+                           int logits_dtype, int batch, const dt_options *opts) {
+  dt_gru g{};
+  g.d_in = d_e;
+  g.d_h = d_h;
+  dt_status st = check_model_shape(V, d_e, &g, weights_dtype);
+  if (st != DT_OK) return st;
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(e, "device query");
+  st = plan_init(p, V, d_e, d_h, weights_dtype, dev, L, M, B, logits_dtype, batch, opts);
+  if (st != DT_OK) return st;
+  if ((long long)batch * L * M >= V || !dt::grow_fits(p, batch))
+    return fail(DT_ERR_UNSUPPORTED, "a one-shot call of this shape needs a plan (dt_plan_create)");
+  return DT_OK;
+}
+
+dt_status dt_once_workspace_size(int V, int d_e, int d_h, int weights_dtype, int L, int M, int B, int logits_dtype,
+                                 int batch, const dt_options *opts, size_t *bytes) {
+  if (!bytes) return fail(DT_ERR_NULL, "bytes is required");
+  dt_plan p{};
+  const dt_status st = once_plan(&p, V, d_e, d_h, weights_dtype, L, M, B, logits_dtype, batch, opts);
+  if (st != DT_OK) return st;
+  OnceWs w{};
+  carve_once(&p, batch, nullptr, &w);
+  *bytes = w.bytes;
+  return DT_OK;
+}
+
+dt_status dt_build_tree_once(const void *emb, int V, int d_e, const dt_gru *gru, const dt_head *head,
+                             int weights_dtype, int L, int M, int B, int logits_dtype, const void *logits, int batch,
+                             const float *h0, float T, const dt_options *opts, void *workspace, size_t ws_bytes,
+                             dt_tree *out, void *stream) {
+  if (!emb || !gru || !head) return fail(DT_ERR_NULL, "emb, gru and head are required");
+  if (!gru->w_ih || !gru->w_hh || !head->w) return fail(DT_ERR_NULL, "w_ih, w_hh and head.w are required");
+  if (gru->d_in != d_e) return fail(DT_ERR_SHAPE, "gru.d_in (%d) must equal d_e (%d)", gru->d_in, d_e);
+  dt_plan p{};
+  dt_status st = once_plan(&p, V, d_e, gru->d_h, weights_dtype, L, M, B, logits_dtype, batch, opts);
+  if (st == DT_OK) st = check_model_align(emb, gru, head, weights_dtype);
+  if (st == DT_OK) st = check_build_args(&p, logits, batch, h0, T, out);
+  if (st != DT_OK) return st;
+  OnceWs w{};
+  carve_once(&p, batch, nullptr, &w);
+  if (!workspace || ws_bytes < w.bytes)
+    return fail(DT_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", w.bytes, workspace ? ws_bytes : 0);
+  if (!aligned(workspace, 256)) return fail(DT_ERR_ALIGN, "workspace must be 256-byte aligned");
+  carve_once(&p, batch, static_cast<char *>(workspace), &w);
+  w.m.emb = emb;
+  p.P_all = w.m.P_all;
+  p.U_all = w.m.U_all;
+  p.c_all = w.m.c_all;
+  p.b_hh = w.m.b_hh;
+  p.whh_t = w.m.whh_t;
+  const float inv_tau = T > 0.0f ? 1.0f / T : 1.0f;
+  const dt::ScanGeom g = dt::scan_geom(batch * L, V, M);
+  const int nbar = (batch + dt::kSlotRows) * dt::kBarStride;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  hipError_t e = dt::pack_weights(&w.m, gru, head, s);
+  if (e == hipSuccess) e = dt::launch_scan_chunks(logits, logits_dtype, g, inv_tau, w.ws, w.ws.bar, 2 * nbar, s);
+  if (e == hipSuccess) e = dt::launch_scan_merge(g, inv_tau, w.ws, s, true);
+  if (e == hipSuccess) e = dt::fold_candidates(&w.m, w.ws.cand, batch * L * M, w.ws.candv, s);
+  if (e == hipSuccess) e = dt::launch_grow(&p, batch, h0, inv_tau, w.ws, out, s, nullptr, nullptr, nullptr, true);
+  if (e != hipSuccess) return hip_fail(e, "one-shot launches");
+  return DT_OK;
 }
 
 dt_status dt_scan_workspace_size(int rows, int V, int M, size_t *bytes) {

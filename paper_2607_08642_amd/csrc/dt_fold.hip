@@ -10,8 +10,9 @@
 //   c[v] = E[v] . b_c
 // This is one GEMM of the embedding table against the packed matrix
 // [W_ih ; W_c^T] ([4 d_h, d_e], K = d_e contiguous).  bf16 weights run on the
-// gfx950 bf16 MFMA (exact products, fp32 accumulation); fp32 weights use a plain
-// FMA kernel.
+// gfx950 bf16 MFMA (exact products, fp32 accumulation); fp32 weights on the fp32
+// MFMA.  A one-shot call (dt_build_tree_once) folds the rows of its candidates
+// only.
 #include "dt_internal.h"
 
 namespace dt {
@@ -24,27 +25,51 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kFoldThreads = 256;
 constexpr int kLdsPad = 8;  // bf16 elements of padding per LDS row
 
+// Tile of a GEMM block, one-dimensional grid: blocks are dealt to the XCDs
+// round-robin, so the column tiles of a row tile are put on one XCD, one after
+// the other, and its embedding rows are read into one L2 (not eight).
+constexpr int kFoldXcds = 8;
+struct FoldTile {
+  int col, row;
+};
+__device__ inline FoldTile fold_tile(int ncol) {
+  const int xcd = blockIdx.x % kFoldXcds, i = blockIdx.x / kFoldXcds;
+  return FoldTile{i % ncol, i / ncol * kFoldXcds + xcd};
+}
+inline dim3 fold_grid(int ncol, int nrow) {
+  return dim3((unsigned)ncol * ((nrow + kFoldXcds - 1) / kFoldXcds * kFoldXcds));
+}
+
 // ---------------------------------------------------------------------------
 // bf16 MFMA GEMM: block tile (WR*TI*32) x (WC*TJ*32), 4 waves as WR x WC.
+// Bound by the LDS round trip of a K slice: the next slice's global loads are
+// issued before the current one is multiplied, so only LDS stands between two
+// slices.  151,936 rows at d_e = 4096, d_h = 512 (2.55 TFLOP): 6.9 ms with the
+// loads in line, 4.2 ms (610 TFLOP/s) ahead and with a row tile kept on one XCD.
+// cadd (nullable): c is also added to cadd[row].
 // ---------------------------------------------------------------------------
 template <int WR, int WC, int TI, int TJ>
 __global__ __launch_bounds__(kFoldThreads) void fold_mfma_kernel(
     const uint16_t *__restrict__ emb, const int32_t *__restrict__ cand, int rows_total, int d_e,
     const uint16_t *__restrict__ wfold, int nf, int d_h, const float *__restrict__ b_ih,
     const float *__restrict__ b_c, float *__restrict__ P, float *__restrict__ U,
-    float *__restrict__ cvec) {
+    float *__restrict__ cvec, float *__restrict__ cadd) {
   static_assert(WR * WC == 4, "4 waves");
   constexpr int BM = WR * TI * 32, BN = WC * TJ * 32, BK = kFoldBK;
   constexpr int LDW = BK + kLdsPad;
+  constexpr int TPR = kFoldThreads / BM;  // threads per row of the E . b_c sums
+  static_assert(TPR * BM == kFoldThreads && BK % (8 * TPR) == 0, "whole 16-byte segments per thread");
   __shared__ __attribute__((aligned(16))) uint16_t As[BM * LDW];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * LDW];
-  __shared__ float bcs[BK];
+  __shared__ __attribute__((aligned(16))) float bcs[BK];
   __shared__ int32_t rowtok[BM];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave / WC, wc = wave % WC;
-  const int n0 = blockIdx.x * BN, r0 = blockIdx.y * BM;
-  const bool do_c = blockIdx.x == 0;  // the first column tile also computes c = E_c b_c
+  const FoldTile tile = fold_tile((nf + BN - 1) / BN);
+  const int n0 = tile.col * BN, r0 = tile.row * BM;
+  if (r0 >= rows_total) return;
+  const bool do_c = tile.col == 0;  // the first column tile also computes c = E_c b_c
 
   for (int i = tid; i < BM; i += kFoldThreads) {
     const int r = r0 + i;
@@ -59,28 +84,44 @@ __global__ __launch_bounds__(kFoldThreads) void fold_mfma_kernel(
     for (int j = 0; j < TJ; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
-  float cacc = 0.0f;  // c[r] partial for rows handled by this thread (do_c only)
+  float cacc = 0.0f;  // c partial of row tid / TPR (do_c only)
 
   constexpr int SEGS = BK / 8;  // 16-byte segments per tile row
-  for (int k0 = 0; k0 < d_e; k0 += BK) {
-    // global -> LDS (gathered A rows, packed B rows)
-    for (int s = tid; s < BM * SEGS; s += kFoldThreads) {
-      const int row = s / SEGS, seg = s % SEGS, k = k0 + seg * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
+  constexpr int NA = BM * SEGS / kFoldThreads, NB = BN * SEGS / kFoldThreads;
+  uint4 ra[NA], rb[NB];
+  float rbc = 0.0f;
+  auto load = [&](int k0) {  // gathered A rows, packed B rows
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const int s = tid + q * kFoldThreads, row = s / SEGS, k = k0 + (s % SEGS) * 8;
       const int tok = rowtok[row];
-      if (tok >= 0 && k + 8 <= d_e) v = *reinterpret_cast<const uint4 *>(emb + (size_t)tok * d_e + k);
-      *reinterpret_cast<uint4 *>(&As[row * LDW + seg * 8]) = v;
+      ra[q] = make_uint4(0, 0, 0, 0);
+      if (tok >= 0 && k + 8 <= d_e) ra[q] = *reinterpret_cast<const uint4 *>(emb + (size_t)tok * d_e + k);
     }
-    for (int s = tid; s < BN * SEGS; s += kFoldThreads) {
-      const int row = s / SEGS, seg = s % SEGS, k = k0 + seg * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int s = tid + q * kFoldThreads, row = s / SEGS, k = k0 + (s % SEGS) * 8;
+      rb[q] = make_uint4(0, 0, 0, 0);
       if (n0 + row < nf && k + 8 <= d_e)
-        v = *reinterpret_cast<const uint4 *>(wfold + (size_t)(n0 + row) * d_e + k);
-      *reinterpret_cast<uint4 *>(&Bs[row * LDW + seg * 8]) = v;
+        rb[q] = *reinterpret_cast<const uint4 *>(wfold + (size_t)(n0 + row) * d_e + k);
     }
-    if (do_c)
-      for (int i = tid; i < BK; i += kFoldThreads) bcs[i] = (k0 + i < d_e) ? b_c[k0 + i] : 0.0f;
+    if (do_c && tid < BK) rbc = k0 + tid < d_e ? b_c[k0 + tid] : 0.0f;
+  };
+  load(0);
+  for (int k0 = 0; k0 < d_e; k0 += BK) {
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const int s = tid + q * kFoldThreads;
+      *reinterpret_cast<uint4 *>(&As[(s / SEGS) * LDW + (s % SEGS) * 8]) = ra[q];
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int s = tid + q * kFoldThreads;
+      *reinterpret_cast<uint4 *>(&Bs[(s / SEGS) * LDW + (s % SEGS) * 8]) = rb[q];
+    }
+    if (do_c && tid < BK) bcs[tid] = rbc;
     __syncthreads();
+    if (k0 + BK < d_e) load(k0 + BK);
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
       bf16x8 a[TI], b[TJ];
@@ -102,14 +143,20 @@ __global__ __launch_bounds__(kFoldThreads) void fold_mfma_kernel(
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
     if (do_c) {
-      // two threads per row, each over half of the K slice
-      for (int i = tid; i < BM * 2; i += kFoldThreads) {
-        const int row = i >> 1, half = i & 1;
-        float s = 0.0f;
-        for (int q = half * (BK / 2); q < (half + 1) * (BK / 2); ++q)
-          s += bf16_to_f32(As[row * LDW + q]) * bcs[q];
-        cacc += s;
+      // TPR threads per row, each over its part of the K slice
+      const int row = tid / TPR, q0 = (tid % TPR) * (BK / TPR);
+      float s = 0.0f;
+#pragma unroll
+      for (int q = q0; q < q0 + BK / TPR; q += 8) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(&As[row * LDW + q]);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s += __uint_as_float(w[e] << 16) * bcs[q + 2 * e];
+          s += __uint_as_float(w[e] & 0xFFFF0000u) * bcs[q + 2 * e + 1];
+        }
       }
+      cacc += s;
     }
     __syncthreads();
   }
@@ -133,21 +180,93 @@ __global__ __launch_bounds__(kFoldThreads) void fold_mfma_kernel(
       }
     }
   }
-  static_assert(BM * 2 <= kFoldThreads, "one (row, half) pair per thread");
   if (do_c) {
-    // thread tid accumulated the half-row pair i = tid; combine the two halves
-    __shared__ float cpart[BM * 2];
-    if (tid < BM * 2) cpart[tid] = cacc;
+    __shared__ float cpart[kFoldThreads];
+    cpart[tid] = cacc;
     __syncthreads();
     for (int row = tid; row < BM; row += kFoldThreads) {
       const int r = r0 + row;
-      if (r < rows_total) cvec[r] = cpart[2 * row] + cpart[2 * row + 1];
+      if (r >= rows_total) continue;
+      float c = cpart[TPR * row];
+#pragma unroll
+      for (int i = 1; i < TPR; ++i) c += cpart[TPR * row + i];
+      cvec[r] = c;
+      if (cadd) cadd[r] += c;
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// generic FMA path (fp32 weights, or widths the MFMA path does not take)
+// fp32 weights: the same GEMM on the fp32 MFMA (32 x 32 x 2), 64 x 64 tiles,
+// K slices of 32, the next slice's loads in flight.  Column nf is b_c: c = E b_c
+// comes out of the same products.  32,003 rows at d_e = 1024, d_h = 256 (67
+// GFLOP): 0.97 ms (69 TFLOP/s); one thread per output, reading its weight row
+// alone, took 127 ms.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kFoldThreads) void fold_f32_kernel(
+    const float *__restrict__ emb, const int32_t *__restrict__ cand, int rows_total, int d_e,
+    const float *__restrict__ wfold, int nf, int d_h, const float *__restrict__ b_ih,
+    const float *__restrict__ b_c, float *__restrict__ P, float *__restrict__ U, float *__restrict__ cvec,
+    float *__restrict__ cadd) {
+  constexpr int BM = 64, BN = 64, BK = 32, LDW = BK + 2;
+  constexpr int NL = BM * BK / kFoldThreads;  // elements per thread and operand
+  __shared__ float As[BM * LDW], Bs[BN * LDW];
+  __shared__ int32_t rowtok[BM];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wr = wave >> 1, wc = wave & 1;
+  const FoldTile tile = fold_tile((nf + 1 + BN - 1) / BN);
+  const int n0 = tile.col * BN, r0 = tile.row * BM;
+  if (r0 >= rows_total) return;
+  if (tid < BM) rowtok[tid] = r0 + tid < rows_total ? (cand ? cand[r0 + tid] : r0 + tid) : -1;
+  __syncthreads();
+  f32x16 acc;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) acc[q] = 0.0f;
+  float ra[NL], rb[NL];
+  // (element e of a slice: row e / 32, column e % 32: a row's 32 floats are one line)
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const int e = tid + q * kFoldThreads, row = e / BK, k = k0 + e % BK, n = n0 + row;
+      const int tok = rowtok[row];
+      ra[q] = (tok >= 0 && k < d_e) ? emb[(size_t)tok * d_e + k] : 0.0f;
+      rb[q] = (n <= nf && k < d_e) ? (n < nf ? wfold[(size_t)n * d_e + k] : b_c[k]) : 0.0f;
+    }
+  };
+  load(0);
+  for (int k0 = 0; k0 < d_e; k0 += BK) {
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const int e = tid + q * kFoldThreads;
+      As[(e / BK) * LDW + e % BK] = ra[q];
+      Bs[(e / BK) * LDW + e % BK] = rb[q];
+    }
+    __syncthreads();
+    if (k0 + BK < d_e) load(k0 + BK);
+    const float *ap = As + (wr * 32 + (lane & 31)) * LDW + (lane >> 5), *bp = Bs + (wc * 32 + (lane & 31)) * LDW + (lane >> 5);
+#pragma unroll
+    for (int k = 0; k < BK; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ap[k], bp[k], acc, 0, 0, 0);
+    __syncthreads();
+  }
+  const int col = n0 + wc * 32 + (lane & 31);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int row = r0 + wr * 32 + (q >> 2) * 8 + (lane >> 5) * 4 + (q & 3);
+    if (row >= rows_total || col > nf) continue;
+    const float v = acc[q];
+    if (col < 3 * d_h)
+      P[(size_t)row * (3 * d_h) + col] = v + b_ih[col];
+    else if (col < nf)
+      U[(size_t)row * d_h + (col - 3 * d_h)] = v;
+    else {
+      cvec[row] = v;
+      if (cadd) cadd[row] += v;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// bf16 rows of a width the 16-byte loads do not take (d_e % 8 != 0)
 // ---------------------------------------------------------------------------
 template <typename TW>
 __device__ inline float wval(const TW *p, size_t i);
@@ -165,7 +284,7 @@ __global__ __launch_bounds__(256) void fold_simple_kernel(
     const TW *__restrict__ emb, const int32_t *__restrict__ cand, int rows_total, int d_e,
     const TW *__restrict__ wfold, int nf, int d_h, const float *__restrict__ b_ih,
     const float *__restrict__ b_c, float *__restrict__ P, float *__restrict__ U,
-    float *__restrict__ cvec) {
+    float *__restrict__ cvec, float *__restrict__ cadd) {
   // one block per candidate row; threads over the nf+1 outputs
   const int r = blockIdx.x;
   if (r >= rows_total) return;
@@ -184,40 +303,51 @@ __global__ __launch_bounds__(256) void fold_simple_kernel(
       P[(size_t)r * (3 * d_h) + n] = s + b_ih[n];
     else if (n < nf)
       U[(size_t)r * d_h + (n - 3 * d_h)] = s;
-    else
+    else {
       cvec[r] = s;
+      if (cadd) cadd[r] += s;
+    }
   }
 }
 
 // ---------------------------------------------------------------------------
 // plan-time packing
 // ---------------------------------------------------------------------------
+// [W_ih ; W_c^T] as rows of K = d_e: W_ih is copied, W_c transposed through LDS in
+// 64 x 64 tiles (element by element, its reads were strided by d_h: 18 us for 10 MB
+// of bf16, 14 us this way).  Rows past 4 d_h are zeros.  blockIdx.x: tiles of
+// columns (k), blockIdx.y: tiles of rows.
 template <typename TW>
-__global__ void pack_wfold_kernel(const TW *__restrict__ w_ih, const TW *__restrict__ w_c, int d_e,
-                                  int d_h, int nf_pad, TW *__restrict__ out) {
-  const size_t total = (size_t)nf_pad * d_e;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const int n = (int)(i / d_e), k = (int)(i % d_e);
-    TW v = TW(0);
-    if (n < 3 * d_h)
-      v = w_ih[(size_t)n * d_e + k];
-    else if (n < 4 * d_h)
-      v = w_c[(size_t)k * d_h + (n - 3 * d_h)];
-    out[i] = v;
+__global__ __launch_bounds__(256) void pack_wfold_kernel(const TW *__restrict__ w_ih, const TW *__restrict__ w_c,
+                                                         int d_e, int d_h, int nf_pad, TW *__restrict__ out) {
+  __shared__ TW tile[64][65];
+  const int k0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
+  const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
+  // (a tile lies in W_ih, or in W_c^T and the rows past it, or across: 3 d_h % 32 == 0)
+  for (int i = y; i < 64; i += 4) {  // W_c row k0 + i, columns n0 + x - 3 d_h
+    const int k = k0 + i, c = n0 + x - 3 * d_h;
+    if (k < d_e && c >= 0 && c < d_h) tile[i][x] = w_c[(size_t)k * d_h + c];
+  }
+  __syncthreads();
+  for (int i = y; i < 64; i += 4) {
+    const int n = n0 + i, k = k0 + x;
+    if (n >= nf_pad || k >= d_e) continue;
+    out[(size_t)n * d_e + k] = n < 3 * d_h ? w_ih[(size_t)n * d_e + k] : (n < 4 * d_h ? tile[x][i] : TW(0));
   }
 }
 
+// b_ih (plus b_hh on the gates r and z), b_hh and b_c in fp32; missing ones are zeros
 template <typename TW>
-__global__ void widen_kernel(const TW *__restrict__ in, int n, float *__restrict__ out) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    out[i] = in ? wval<TW>(in, i) : 0.0f;
-}
-
-// dst[i] += src[i]: folds b_hh's r and z parts into the input-side bias
-__global__ void add_kernel(float *__restrict__ dst, const float *__restrict__ src, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    dst[i] += src[i];
+__global__ void pack_bias_kernel(const TW *__restrict__ b_ih, const TW *__restrict__ b_hh, const TW *__restrict__ b_c,
+                                 int d_h, int d_e, float *__restrict__ o_ih, float *__restrict__ o_hh,
+                                 float *__restrict__ o_c) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 3 * d_h) {
+    const float h = b_hh ? wval<TW>(b_hh, i) : 0.0f, x = b_ih ? wval<TW>(b_ih, i) : 0.0f;
+    o_hh[i] = h;
+    o_ih[i] = i < 2 * d_h ? x + h : x;
+  }
+  if (i < d_e) o_c[i] = b_c ? wval<TW>(b_c, i) : 0.0f;
 }
 
 // W_hh packed in MFMA A-fragment order for the expansion kernel.
@@ -269,57 +399,58 @@ inline int grid_for(size_t n) {
 
 hipError_t pack_weights(dt_model *p, const dt_gru *gru, const dt_head *head, hipStream_t s) {
   const int d_e = p->d_e, d_h = p->d_h;
-  const size_t wfold_n = (size_t)p->nf_pad * d_e;
+  const dim3 tiles((d_e + 63) / 64, (p->nf_pad + 63) / 64), block(256);
+  const int nbias = grid_for((size_t)(3 * d_h > d_e ? 3 * d_h : d_e)), nwhh = grid_for((size_t)3 * d_h * d_h);
   if (p->wdt == DT_BF16) {
-    hipLaunchKernelGGL(pack_wfold_kernel<uint16_t>, dim3(grid_for(wfold_n)), dim3(256), 0, s,
-                       (const uint16_t *)gru->w_ih, (const uint16_t *)head->w, d_e, d_h, p->nf_pad,
-                       (uint16_t *)p->wfold);
-    hipLaunchKernelGGL(widen_kernel<uint16_t>, dim3(grid_for(3 * d_h)), dim3(256), 0, s,
-                       (const uint16_t *)gru->b_ih, 3 * d_h, p->b_ih);
-    hipLaunchKernelGGL(widen_kernel<uint16_t>, dim3(grid_for(3 * d_h)), dim3(256), 0, s,
-                       (const uint16_t *)gru->b_hh, 3 * d_h, p->b_hh);
-    hipLaunchKernelGGL(widen_kernel<uint16_t>, dim3(grid_for(d_e)), dim3(256), 0, s,
-                       (const uint16_t *)head->b, d_e, p->b_c);
-    hipLaunchKernelGGL(pack_whh_bf16_kernel, dim3(grid_for((size_t)3 * d_h * d_h)), dim3(256), 0,
-                       s, (const uint16_t *)gru->w_hh, d_h, (uint16_t *)p->whh_t);
+    hipLaunchKernelGGL(pack_wfold_kernel<uint16_t>, tiles, block, 0, s, (const uint16_t *)gru->w_ih,
+                       (const uint16_t *)head->w, d_e, d_h, p->nf_pad, (uint16_t *)p->wfold);
+    hipLaunchKernelGGL(pack_bias_kernel<uint16_t>, dim3(nbias), block, 0, s, (const uint16_t *)gru->b_ih,
+                       (const uint16_t *)gru->b_hh, (const uint16_t *)head->b, d_h, d_e, p->b_ih, p->b_hh, p->b_c);
+    hipLaunchKernelGGL(pack_whh_bf16_kernel, dim3(nwhh), block, 0, s, (const uint16_t *)gru->w_hh, d_h,
+                       (uint16_t *)p->whh_t);
   } else {
-    hipLaunchKernelGGL(pack_wfold_kernel<float>, dim3(grid_for(wfold_n)), dim3(256), 0, s,
-                       (const float *)gru->w_ih, (const float *)head->w, d_e, d_h, p->nf_pad,
-                       (float *)p->wfold);
-    hipLaunchKernelGGL(widen_kernel<float>, dim3(grid_for(3 * d_h)), dim3(256), 0, s,
-                       (const float *)gru->b_ih, 3 * d_h, p->b_ih);
-    hipLaunchKernelGGL(widen_kernel<float>, dim3(grid_for(3 * d_h)), dim3(256), 0, s,
-                       (const float *)gru->b_hh, 3 * d_h, p->b_hh);
-    hipLaunchKernelGGL(widen_kernel<float>, dim3(grid_for(d_e)), dim3(256), 0, s,
-                       (const float *)head->b, d_e, p->b_c);
-    hipLaunchKernelGGL(pack_whh_f32_kernel, dim3(grid_for((size_t)3 * d_h * d_h)), dim3(256), 0, s,
-                       (const float *)gru->w_hh, d_h, (float *)p->whh_t);
+    hipLaunchKernelGGL(pack_wfold_kernel<float>, tiles, block, 0, s, (const float *)gru->w_ih,
+                       (const float *)head->w, d_e, d_h, p->nf_pad, (float *)p->wfold);
+    hipLaunchKernelGGL(pack_bias_kernel<float>, dim3(nbias), block, 0, s, (const float *)gru->b_ih,
+                       (const float *)gru->b_hh, (const float *)head->b, d_h, d_e, p->b_ih, p->b_hh, p->b_c);
+    hipLaunchKernelGGL(pack_whh_f32_kernel, dim3(nwhh), block, 0, s, (const float *)gru->w_hh, d_h,
+                       (float *)p->whh_t);
   }
-  hipLaunchKernelGGL(add_kernel, dim3(grid_for(2 * d_h)), dim3(256), 0, s, p->b_ih, p->b_hh, 2 * d_h);
   return hipGetLastError();
 }
 
-hipError_t fold_vocab(const dt_model *p, hipStream_t s) {
-  const int rows_total = p->V;
-  const float *bc = p->b_c;  // zeros when the head has no bias
-  if (p->wdt == DT_BF16 && p->d_e % 8 == 0) {
-    const int ntile_n = (p->nf + 127) / 128;
-    dim3 grid(ntile_n, (rows_total + 127) / 128);
-    hipLaunchKernelGGL((fold_mfma_kernel<2, 2, 2, 2>), grid, dim3(kFoldThreads), 0, s,
-                       (const uint16_t *)p->emb, nullptr, rows_total, p->d_e,
-                       (const uint16_t *)p->wfold, p->nf, p->d_h, p->b_ih, bc, p->P_all, p->U_all,
-                       p->c_all);
-  } else if (p->wdt == DT_BF16) {
-    hipLaunchKernelGGL(fold_simple_kernel<uint16_t>, dim3(rows_total), dim3(256), 0, s,
-                       (const uint16_t *)p->emb, nullptr, rows_total, p->d_e,
-                       (const uint16_t *)p->wfold, p->nf, p->d_h, p->b_ih, bc, p->P_all, p->U_all,
-                       p->c_all);
+// Fold `rows` embedding rows: all of the vocabulary (cand null), or those of the
+// ids in cand (-1: a row of zeros).  cadd: see fold_mfma_kernel.
+static hipError_t launch_fold(const dt_model *p, const int32_t *cand, int rows, float *cadd, hipStream_t s) {
+  const dim3 block(kFoldThreads);
+  if (p->wdt == DT_F32) {
+    hipLaunchKernelGGL(fold_f32_kernel, fold_grid((p->nf + 1 + 63) / 64, (rows + 63) / 64), block, 0, s,
+                       (const float *)p->emb, cand, rows, p->d_e, (const float *)p->wfold, p->nf, p->d_h, p->b_ih,
+                       p->b_c, p->P_all, p->U_all, p->c_all, cadd);
+  } else if (p->d_e % 8 == 0) {
+    // 128 x 128 tiles while they fill the chip twice over; smaller ones leave fewer
+    // CUs idle (1,024 rows: 128 against 512 tiles)
+    const int t128 = ((p->nf + 127) / 128) * ((rows + 127) / 128);
+    if (t128 >= 512)
+      hipLaunchKernelGGL((fold_mfma_kernel<2, 2, 2, 2>), fold_grid((p->nf + 127) / 128, (rows + 127) / 128), block, 0, s,
+                         (const uint16_t *)p->emb, cand, rows, p->d_e, (const uint16_t *)p->wfold, p->nf, p->d_h,
+                         p->b_ih, p->b_c, p->P_all, p->U_all, p->c_all, cadd);
+    else
+      hipLaunchKernelGGL((fold_mfma_kernel<2, 2, 1, 1>), fold_grid((p->nf + 63) / 64, (rows + 63) / 64), block, 0, s,
+                         (const uint16_t *)p->emb, cand, rows, p->d_e, (const uint16_t *)p->wfold, p->nf, p->d_h,
+                         p->b_ih, p->b_c, p->P_all, p->U_all, p->c_all, cadd);
   } else {
-    hipLaunchKernelGGL(fold_simple_kernel<float>, dim3(rows_total), dim3(256), 0, s,
-                       (const float *)p->emb, nullptr, rows_total, p->d_e, (const float *)p->wfold,
-                       p->nf, p->d_h, p->b_ih, bc, p->P_all, p->U_all, p->c_all);
+    hipLaunchKernelGGL(fold_simple_kernel<uint16_t>, dim3(rows), dim3(256), 0, s, (const uint16_t *)p->emb, cand,
+                       rows, p->d_e, (const uint16_t *)p->wfold, p->nf, p->d_h, p->b_ih, p->b_c, p->P_all, p->U_all,
+                       p->c_all, cadd);
   }
   return hipGetLastError();
+}
+
+hipError_t fold_vocab(const dt_model *p, hipStream_t s) { return launch_fold(p, nullptr, p->V, nullptr, s); }
+
+hipError_t fold_candidates(const dt_model *p, const int32_t *cand, int rows, float *candv, hipStream_t s) {
+  return launch_fold(p, cand, rows, candv, s);
 }
 
 }  // namespace dt

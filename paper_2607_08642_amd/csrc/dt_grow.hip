@@ -73,6 +73,7 @@ static_assert(GW == 4 && CH == 16 && UW == 32, "the work split below");
 
 struct GrowArgs {
   int L, M, B, k, G, norm_mode, pos_offset, batch, nchunks, nxcd, ngroups, spin_limit;
+  int compact;     // rows merged by an earlier launch; table rows are candidate slots
   float inv_tau, c2;
   const uint64_t *ckeys;
   const float2 *ctail;
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
     ints[I_CNT1] = 0;
   }
   int cell = member;  // rows of the group's trees, dealt to its members
-  for (int t = group; t < a.batch; t += a.ngroups) {
+  for (int t = group; t < a.batch && !a.compact; t += a.ngroups) {
     for (; cell < L; cell += G) {
       const int row = t * L + cell;
       sel::merge_row_tree<true, GT, true>(a.ckeys + (size_t)row * a.nchunks * M, a.nchunks, M,
@@ -486,7 +487,8 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int d = d0 + i * GW < L ? d0 + i * GW : L - 1;
-          ids[d * MP + lane] = (int)id[i] > 0 ? (int)id[i] : 0;  // dead slots (-1): row 0, unused
+          // (dead slots, -1: row 0, unused)
+          ids[d * MP + lane] = a.compact ? (t * L + d) * M + m : max((int)id[i], 0);
           vals[d * MP + lane] = lane < M ? as_f(v[i]) : NEG_INF;
         }
       }
@@ -943,7 +945,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
     if (wave == 0) {
       const int dep = e_meta & 127, m = 63 - (int)((e_lo >> 13) & 63u);
       if (lane < B) {
-        otok[lane] = emit ? ids[(dep - 1) * MP + m] : -1;
+        otok[lane] = !emit ? -1 : a.compact ? a.cand[ids[(dep - 1) * MP + m]] : ids[(dep - 1) * MP + m];
         opar[lane] = parent;
         odep[lane] = emit ? dep : 0;
         opos[lane] = a.pos_offset + (emit ? dep : 0);
@@ -1036,8 +1038,10 @@ size_t grow_part_bytes(const dt_plan *p, int batch) {
 }
 
 hipError_t launch_grow(const dt_plan *p, int batch, const float *h0, float inv_tau, const Workspace &ws,
-                       const dt_tree *out, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int32_t *stats) {
+                       const dt_tree *out, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int32_t *stats,
+                       bool compact) {
   GrowArgs a;
+  a.compact = compact;
   a.L = p->L;
   a.M = p->M;
   a.B = p->B;

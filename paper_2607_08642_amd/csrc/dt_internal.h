@@ -177,8 +177,13 @@ hipError_t launch_scan_chunks(const void *logits, int ldt, const ScanGeom &g, fl
                               const Workspace &ws, int32_t *zero_ptr, int zero_n, hipStream_t s,
                               hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr,
                               const HeadProj *hp = nullptr);
-hipError_t launch_scan_merge(const ScanGeom &g, float inv_tau, const Workspace &ws, hipStream_t s);
+// (shift: candidate values and tails less the row's largest value, as the expansion takes them)
+hipError_t launch_scan_merge(const ScanGeom &g, float inv_tau, const Workspace &ws, hipStream_t s,
+                             bool shift = false);
 hipError_t fold_vocab(const dt_model *m, hipStream_t s);
+// the rows of the ids in cand [rows] (-1: zeros) into the first `rows` rows of the
+// tables; each row's E . b_c is added to candv[row]
+hipError_t fold_candidates(const dt_model *m, const int32_t *cand, int rows, float *candv, hipStream_t s);
 // Domino-head path (dt_build_tree_head): heap entries per tree, workspace, launch
 constexpr int kHeadCap = 4096;
 struct HeadWorkspace {
@@ -230,14 +235,16 @@ int expand_group_size(const dt_plan *p, int batch);
 size_t expand_lds_bytes(int dh, int G, int M, int nchunks, int L, int rj = 0, int wbytes = 0);
 size_t expand_part_bytes(const dt_plan *p, int batch);
 // the register-list expansion: whether a call takes it, its groups of workgroups,
-// workspace and launch
+// workspace and launch (compact: the rows are merged, and the tables hold a row
+// for every candidate slot, (t L + d) M + m, instead of the vocabulary)
 bool grow_fits(const dt_plan *p, int batch);
 int grow_max_occ(int wdt, int d_h, int L, int B, int num_cus, int num_xcd);
 int grow_groups(const dt_plan *p, int batch);
 size_t grow_state_bytes(const dt_plan *p, int batch);
 size_t grow_part_bytes(const dt_plan *p, int batch);
 hipError_t launch_grow(const dt_plan *p, int batch, const float *h0, float inv_tau, const Workspace &ws,
-                       const dt_tree *out, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int32_t *stats);
+                       const dt_tree *out, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int32_t *stats,
+                       bool compact = false);
 hipError_t pack_weights(dt_model *m, const dt_gru *gru, const dt_head *head, hipStream_t s);
 
 }  // namespace dt

@@ -981,7 +981,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
   }
 }
 
-// K2 (dt_scan_topm only): merge the chunk lists of one row
+// K2 (dt_scan_topm and one-shot calls): merge the chunk lists of one row
+template <bool SHIFT>
 __global__ __launch_bounds__(kScanThreads) void scan_merge_kernel(
     ScanGeom g, float c, float inv_tau, const uint64_t *__restrict__ ckeys,
     const float2 *__restrict__ ctail, const int32_t *__restrict__ cflag, int32_t *__restrict__ cand,
@@ -990,7 +991,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_merge_kernel(
   __shared__ float2 red[kWaves];
   __shared__ int flag;
   const int row = blockIdx.x;
-  sel::merge_row<kScanThreads, false>(ckeys + (size_t)row * g.nchunks * g.M, g.nchunks, g.M,
+  sel::merge_row<kScanThreads, false, SHIFT>(ckeys + (size_t)row * g.nchunks * g.M, g.nchunks, g.M,
                                       ctail + (size_t)row * g.nchunks, cflag + (size_t)row * g.nchunks,
                                       c, inv_tau, sortbuf, red, &flag, cand + (size_t)row * g.M,
                                       candv + (size_t)row * g.M, tailR + row, rflag + row,
@@ -1132,13 +1133,13 @@ hipError_t launch_scan_chunks(const void *logits, int ldt, const ScanGeom &g, fl
   return hipGetLastError();
 }
 
-hipError_t launch_scan_merge(const ScanGeom &g, float inv_tau, const Workspace &ws, hipStream_t s) {
+hipError_t launch_scan_merge(const ScanGeom &g, float inv_tau, const Workspace &ws, hipStream_t s, bool shift) {
   const float c = 1.4426950408889634f * inv_tau;
   const size_t lds = merge_lds_bytes(g);
-  hipError_t e = hipFuncSetAttribute((const void *)scan_merge_kernel,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const auto kernel = shift ? scan_merge_kernel<true> : scan_merge_kernel<false>;
+  hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(scan_merge_kernel, dim3(g.rows), dim3(kScanThreads), lds, s, g, c, inv_tau,
+  hipLaunchKernelGGL(kernel, dim3(g.rows), dim3(kScanThreads), lds, s, g, c, inv_tau,
                      ws.chunk_keys, ws.chunk_tail, ws.chunk_flag, ws.cand, ws.candv, ws.tail,
                      ws.row_flag);
   return hipGetLastError();
