@@ -710,8 +710,10 @@ dt_status dt_scan_topm(const void *logits, int rows, int V, int logits_dtype, in
   ws.row_flag = row_flags;
   const float inv_tau = T > 0.0f ? 1.0f / T : 1.0f;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = dt::launch_scan_chunks(logits, logits_dtype, g, inv_tau, ws, nullptr, 0, s);
-  if (e == hipSuccess) e = dt::launch_scan_merge(g, inv_tau, ws, s);
+  const bool direct = g.nchunks == 1;  // (a row of one segment needs no merge)
+  hipError_t e = dt::launch_scan_chunks(logits, logits_dtype, g, inv_tau, ws, nullptr, 0, s, nullptr, nullptr,
+                                        nullptr, direct);
+  if (e == hipSuccess && !direct) e = dt::launch_scan_merge(g, inv_tau, ws, s);
   if (e != hipSuccess) return hip_fail(e, "scan launch");
   return DT_OK;
 }

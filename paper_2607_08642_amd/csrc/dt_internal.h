@@ -24,9 +24,7 @@ constexpr int kMaxDe = 8192;
 constexpr int kScanThreads = 256;
 constexpr int kScanPerThread = 40;                         // elements held per thread
 constexpr int kScanChunk = kScanThreads * kScanPerThread;  // 10240
-constexpr int kScanSortCap = 4096;   // bitonic sort buffer (keys) per workgroup
 constexpr int kScanSlots = 1024;    // scan workgroups resident at once (4 per CU of 256)
-constexpr int kScanFlushAt = 256;    // fallback: flush the candidate buffer beyond this
 constexpr int kMergeLdsMax = 96 * 1024;  // row merge buffer (sel::merge_buf_bytes) at most
 
 // fold GEMM tile (bf16 MFMA path)
@@ -173,10 +171,12 @@ struct HeadProj {
 HeadProj head_proj_args(const dt_plan *p, int rows, const void *H, const dt_domino_head &hd, float *a_out);
 // kernel launchers; with t0/t1 the launch records HIP events at the kernel's
 // start and end (hipExtLaunchKernel), used for stage timing
+// direct (rows of one segment only): the merged rows (ws.cand, candv, tail, row_flag)
+// instead of segment lists
 hipError_t launch_scan_chunks(const void *logits, int ldt, const ScanGeom &g, float inv_tau,
                               const Workspace &ws, int32_t *zero_ptr, int zero_n, hipStream_t s,
                               hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr,
-                              const HeadProj *hp = nullptr);
+                              const HeadProj *hp = nullptr, bool direct = false);
 // (shift: candidate values and tails less the row's largest value, as the expansion takes them)
 hipError_t launch_scan_merge(const ScanGeom &g, float inv_tau, const Workspace &ws, hipStream_t s,
                              bool shift = false);

@@ -1,33 +1,49 @@
 // S1: per-depth marginal top-M and the tail log-sum-exp (Alg. 1 step 1;
 // section 3.2, candidate restriction).
 //
-// Each logit row [V] is cut into segments of one or more batches of 10240
-// elements; a 256-thread workgroup streams its segment's batches through
-// registers (40 values per thread, the next batch always in flight) against a
-// running exact top-M list:
-//   * keys are 64-bit (order-preserving value bits, ~index), so the order
-//     (value desc, id asc) is a plain integer order without ties;
-//   * first batch: every wave finds the ceil(M/4)-th largest of its 64 per-lane
-//     maxima (a bitwise search with one ballot per bit); the minimum over the
-//     4 waves leaves at least M elements at or above it, so it is an exact
-//     lower bound on the batch's M-th best element;  later batches: the list's
-//     M-th value;
-//   * one pass over the registers sends every element below that threshold
-//     into the running tail sum (max, sum exp((x - max)/tau)); the few above
-//     it are appended, as keys, to a per-wave region of LDS through the
-//     comparison's lane mask;
-//   * the regions are merged into the list after the first batch, once about
-//     2M candidates have gathered, and at the end.  For M <= 64 each wave
-//     sorts its region in registers (bitonic, 64 keys per lane-set) and the
-//     wave lists and the list meet in a tree of bitonic merges; larger M ranks
-//     every candidate by counting the larger ones (or sorts when there are
-//     many).  Keys that drop out of the list join the tail.
-// If a wave's candidates overflow its region (adversarial rows: long runs of
-// equal or monotone values), the batch is streamed through a bounded selector
-// that keeps a sorted list of M.
-// The per-row merge of the segment lists (merge_row and its register
-// variants) runs inside the expansion kernel, or in a small kernel of its own
-// for dt_scan_topm.
+// Each logit row [V] is cut into segments of one or more batches (40 elements
+// per thread); a workgroup of W waves streams its segment's batches through
+// registers, the next batch always in flight.  Keys are 64-bit (order-preserving
+// value bits, ~index), so the order (value desc, id asc) is a plain integer order
+// without ties.  Every wave keeps its own list of its 64 R best keys in registers
+// (M <= 64 R; entry r * 64 + lane, descending) and merges its own candidates into
+// it when they gather -- no block barrier while the segment streams, so a wave
+// that merges does not hold up the other waves' loads.  A candidate must beat a
+// lower bound on the segment's M-th key:
+//   * the bound tb of the first two batches (every wave: the ceil(M/W)-th largest
+//     of its 64 lanes' maxima over both, found bit by bit with one ballot each;
+//     the minimum over the waves leaves at least M elements at or above it; the
+//     one block barrier), ties kept.  Drawn from twice the elements, it admits
+//     about 40% fewer candidates over an eight-batch segment of Gaussian-like
+//     logits than the first batch's alone;
+//   * the wave's own list's M-th value, strictly: the wave's later elements
+//     have larger indices, so they lose ties with its own list.
+// Both depend on nothing but the data, so the candidates, the merges and the
+// order of every tail sum are the same from run to run.  (Reading the other
+// waves' list values as they stood was faster -- 40.2 against 43.3 us on 512
+// rows of 151936 bf16 logits -- but made the candidates, and with them the
+// tails' rounding, depend on timing; reading them two batches late, waiting
+// for them, gained nothing over the own bound.)
+//   * one pass over a batch's registers sends every element at or below the bound
+//     into the running tail sum and the few above it, as (index, value) pairs, to
+//     the wave's region of LDS through the comparison's lane mask;
+//   * a wave merges once 48 candidates have gathered (64 for longer lists): a
+//     bitonic sort of 64 keys, then bitonic merges whose losers join the tail;
+//   * the wave lists meet once, at the end of the segment, in a tree.
+// A wave whose candidates overflow its region (adversarial rows: long runs of
+// equal or monotone values) re-reads the batch and merges as it goes; a first
+// batch without a finite bound (mostly -inf or padding) takes every element in
+// range as a candidate that way.
+//
+// Rows need no alignment: a row is read from the 16-byte boundary at or below
+// its first element, the elements before it (and past its end) made -inf in
+// registers.  Those bytes share a 16-byte granule with the row's own, so the
+// loads stay on pages that hold the row.  (Reading such rows element by element
+// took 64.6 us for 128 rows of 151937 bf16 at M = 128; see launch_scan_chunks.)
+//
+// The per-row merge of the segment lists (merge_row and its register variants)
+// runs inside the expansion kernels, or in a small kernel of its own for
+// dt_scan_topm; a row of one segment needs none there (its list is the result).
 //
 // For Domino's own head the launch carries extra workgroups (blockIdx.x >=
 // nchunks) that compute a[row][r] = W_1^H H_row, the half of W_1 [H_d; S] that
@@ -44,7 +60,7 @@ namespace {
 
 using sel::Tail;
 
-constexpr int kWaves = kScanThreads / 64;
+constexpr int kProjWaves = kScanThreads / 64;  // (launches with a projection: 256 threads)
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -53,7 +69,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // row tile) with fp32 accumulation: the K = d_H columns split over the waves
 // in chunks of KC (one MFMA group: lane l holds KC/4 consecutive columns of
 // rank (tile row) l % 16 and of H row l % 16, at column group l / 16), the
-// wave partials summed in LDS (red: kWaves x 256 floats).  Out-of-range ranks,
+// wave partials summed in LDS (red: kProjWaves x 256 floats).  Out-of-range ranks,
 // rows and columns read as zeros and are not stored.  bf16: 16x16x32 bf16
 // MFMAs on the stored values (exact products); fp32: 16x16x4 fp32 MFMAs.
 template <typename TW>
@@ -72,12 +88,12 @@ __device__ void head_proj_tile(const HeadProj &p, int rows, int tile, float *red
   using V = typename std::conditional<kBf, uint4, float4>::type;  // KL columns
   const int nch = (p.d_H + KC - 1) / KC;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int c0 = w; c0 < nch; c0 += kWaves * U) {
+  for (int c0 = w; c0 < nch; c0 += kProjWaves * U) {
     V av[U], bv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int k = (c0 + u * kWaves) * KC + g * KL;  // (d_H % 8 == 0: a lane's KL are all in or out)
-      const bool ok = c0 + u * kWaves < nch && k < p.d_H;
+      const int k = (c0 + u * kProjWaves) * KC + g * KL;  // (d_H % 8 == 0: a lane's KL are all in or out)
+      const bool ok = c0 + u * kProjWaves < nch && k < p.d_H;
       av[u] = (ok && rok) ? *reinterpret_cast<const V *>(wr + k) : V{};
       bv[u] = (ok && qok) ? *reinterpret_cast<const V *>(hr + k) : V{};
     }
@@ -101,86 +117,9 @@ __device__ void head_proj_tile(const HeadProj &p, int rows, int tile, float *red
   static_assert(kScanThreads == 256, "one thread per tile element");
   const int e = threadIdx.x, el = e >> 2, ei = e & 3;
   float sum = red[e];
-  for (int v = 1; v < kWaves; ++v) sum += red[v * 256 + e];
+  for (int v = 1; v < kProjWaves; ++v) sum += red[v * 256 + e];
   const int rr = rt * 16 + (el >> 4) * 4 + ei, qq = qt * 16 + (el & 15);
   if (rr < p.rank && qq < rows) p.a[(size_t)qq * p.rank + rr] = sum;
-}
-
-constexpr int kRegion = kScanSortCap / kWaves;       // candidate keys per wave
-constexpr int kRegionCap = kRegion - kMaxM / kWaves;  // fill limit: the list fits beside them
-// a merge is due once this many times M candidates have gathered (measured best
-// at 2 for Qwen3 shapes: 1, 4 and 8 were slower)
-constexpr int kMergeAt = 2;
-
-struct ScanLDS {
-  alignas(16) uint64_t buf[kScanSortCap];
-  float2 red[kWaves];
-  // per-wave candidate counts, by batch parity: a wave can start the next batch
-  // (and write its counts) while another still reads this batch's
-  int wcnt[2][kWaves];
-  int wprev[2][kWaves];
-  int nbuf;
-  int nlist;
-  int flag;
-  uint64_t thr;
-};
-
-// ---------------------------------------------------------------------------
-// bounded streaming selector (fallback for chunks whose survivors overflow):
-// buf[0..nlist) is the sorted best-M list, buf[nlist..nbuf) new candidates
-// ---------------------------------------------------------------------------
-__device__ void flush(ScanLDS &sh, int M, Tail &tail, float c) {
-  const int tid = threadIdx.x;
-  const int n = sh.nbuf;
-  const int P = sel::pow2_at_least(n, 64);
-  for (int i = n + tid; i < P; i += kScanThreads) sh.buf[i] = 0;
-  __syncthreads();
-  sel::block_sort_desc<kScanThreads>(sh.buf, P);
-  for (int i = M + tid; i < n; i += kScanThreads) sel::tail_add1(tail, key_value(sh.buf[i]), c);
-  __syncthreads();
-  if (tid == 0) {
-    const int nl = n < M ? n : M;
-    sh.nlist = nl;
-    sh.nbuf = nl;
-    if (nl == M) {
-      const uint64_t t = sh.buf[M - 1] + 1;
-      if (t > sh.thr) sh.thr = t;
-    }
-  }
-  __syncthreads();
-}
-
-// one group of EPT keys per thread (0 = none); keys below the running
-// threshold join the tail, the others the candidate buffer
-template <int EPT>
-__device__ void stream_batch(ScanLDS &sh, const uint64_t (&key)[EPT], const float (&val)[EPT],
-                             int M, Tail &tail, float c) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t thr = sh.thr;
-  float tv[EPT];
-  uint64_t bal[EPT];
-  int tot = 0;
-#pragma unroll
-  for (int j = 0; j < EPT; ++j) {
-    const bool pass = key[j] != 0 && key[j] >= thr;
-    tv[j] = (key[j] != 0 && !pass) ? val[j] : -__builtin_huge_valf();
-    bal[j] = __ballot(pass);
-    tot += __popcll(bal[j]);
-  }
-  sel::tail_add_group<EPT>(tail, tv, c);
-  if (tot) {
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&sh.nbuf, tot);
-    base = __shfl(base, 0);
-    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-      if ((bal[j] >> lane) & 1ull) sh.buf[base + __popcll(bal[j] & below)] = key[j];
-      base += __popcll(bal[j]);
-    }
-  }
-  __syncthreads();
-  if (sh.nbuf - sh.nlist > kScanFlushAt) flush(sh, M, tail, c);
 }
 
 template <typename T>
@@ -227,65 +166,58 @@ struct Raw {
   uint4 q[NL];
 };
 
-// Issue the loads of one batch (element (j, e) of this thread sits at batch
-// offset j*STEP + tid*EPL + e); nothing waits for them here.
-template <typename T, bool VEC>
-__device__ inline void load_batch(Raw<T> &r, const T *base, int bn) {
+// Issue the loads of batch `b` of a segment (element (j, e) of this thread sits at
+// batch offset j*STEP + tid*EPL + e): straight-line 16-byte buffer loads; loads
+// past the segment's granules return zeros and cost no traffic, and pad_batch
+// makes what lies outside the row -inf.  Nothing waits for the data here.
+template <typename T, int W>
+__device__ inline void load_batch(Raw<T> &r, __amdgpu_buffer_rsrc_t seg, int b) {
   constexpr int EPL = Elem<T>::EPL;
-  constexpr int STEP = kScanThreads * EPL;
-  int lb = threadIdx.x * EPL;
-  asm volatile("" : "+v"(lb));
-#pragma unroll
-  for (int j = 0; j < Raw<T>::NL; ++j) {
-    const int off = lb + j * STEP;
-    if (VEC && off + EPL <= bn) {
-      r.q[j] = *reinterpret_cast<const uint4 *>(base + off);
-    } else {
-      uint32_t w[4] = {0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};  // bf16 -inf pairs
-      if constexpr (EPL == 8) {
-        const uint16_t *b16 = reinterpret_cast<const uint16_t *>(base);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t h = off + e < bn ? (uint32_t)b16[off + e] : 0xFF80u;
-          w[e >> 1] = (e & 1) ? ((w[e >> 1] & 0xFFFFu) | (h << 16)) : ((w[e >> 1] & 0xFFFF0000u) | h);
-        }
-      } else {
-        const float *f = reinterpret_cast<const float *>(base);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          w[e] = __float_as_uint(off + e < bn ? f[off + e] : -__builtin_huge_valf());
-      }
-      r.q[j] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-  }
-}
-
-// 16-byte-aligned rows: straight-line buffer loads of batch `b` of a segment
-// (seg_bytes of data from `seg`); loads past the segment's end return zeros
-// (each 16-byte load lies wholly inside or outside it) and are made -inf by
-// pad_batch.  Nothing waits for the data here.
-template <typename T>
-__device__ inline void load_batch_vec(Raw<T> &r, __amdgpu_buffer_rsrc_t seg, int b) {
-  constexpr int EPL = Elem<T>::EPL;
-  constexpr int STEP = kScanThreads * EPL;
+  constexpr int STEP = W * 64 * EPL;
   int lb = (int)threadIdx.x * EPL;
   asm volatile("" : "+v"(lb));
-  const int base = (b * kScanChunk + lb) * (int)sizeof(T);
+  const int base = (b * (W * 64 * kScanPerThread) + lb) * (int)sizeof(T);
 #pragma unroll
   for (int j = 0; j < Raw<T>::NL; ++j)
     r.q[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
                                            seg, base + j * STEP * (int)sizeof(T), 0, 0));
 }
 
-// the elements of a partial batch past its end become -inf
+// 16 bytes with the elements outside [lo, hi) made -inf
 template <typename T>
-__device__ inline void pad_batch(Raw<T> &r, int bn) {
-  constexpr int EPL = Elem<T>::EPL;
-  constexpr int STEP = kScanThreads * EPL;
-  const uint32_t ninf = EPL == 8 ? 0xFF80FF80u : 0xFF800000u;
+__device__ inline uint4 pad_granule(uint4 q, int lo, int hi) {
+  constexpr int PER = 4 / sizeof(T);  // elements per dword
+  uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-  for (int j = 0; j < Raw<T>::NL; ++j)
-    if ((int)threadIdx.x * EPL + j * STEP >= bn) r.q[j] = make_uint4(ninf, ninf, ninf, ninf);
+  for (int i = 0; i < 4; ++i) {
+    const int e = i * PER;
+    if constexpr (PER == 2) {
+      if (e < lo || e >= hi) w[i] = (w[i] & 0xFFFF0000u) | 0xFF80u;
+      if (e + 1 < lo || e + 1 >= hi) w[i] = (w[i] & 0xFFFFu) | 0xFF800000u;
+    } else {
+      if (e < lo || e >= hi) w[i] = 0xFF800000u;
+    }
+  }
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// the elements of a batch before `lo` and from `hi` on become -inf (lo < EPL)
+template <typename T, int W>
+__device__ inline void pad_batch(Raw<T> &r, int lo, int hi) {
+  constexpr int EPL = Elem<T>::EPL;
+  constexpr int STEP = W * 64 * EPL;
+  constexpr uint32_t ninf = EPL == 8 ? 0xFF80FF80u : 0xFF800000u;
+  int lb = (int)threadIdx.x * EPL;
+  asm volatile("" : "+v"(lb));
+  if (lo > 0 && threadIdx.x == 0) r.q[0] = pad_granule<T>(r.q[0], lo, EPL);
+#pragma unroll
+  for (int j = 0; j < Raw<T>::NL; ++j) {
+    // (whole granules past the end, and the one that holds it)
+    if (hi < (j + 1) * STEP) {  // (uniform)
+      const int in = hi - j * STEP - lb;
+      if (in < EPL) r.q[j] = in <= 0 ? make_uint4(ninf, ninf, ninf, ninf) : pad_granule<T>(r.q[j], 0, in);
+    }
+  }
 }
 
 // Opaque to the compiler: each pass unpacks the elements again (one ALU op each)
@@ -308,435 +240,7 @@ __device__ inline float elem(const Raw<T> &r, int j, int e) {
   }
 }
 
-// K1: exact top-M of one segment (g.chunk elements: one or more batches of
-// kScanChunk) of one row, plus the tail of the rest.  The segment's batches
-// stream through registers (the next batch loads while this one is processed)
-// against a running top-M list:
-//   first batch  the value threshold above, then a rank pass;
-//   later ones   only elements above the list's M-th value can enter (later
-//                elements lose ties on the index); they are ranked into the list
-//                and whatever drops out joins the tail.
-// The tail of the elements below the threshold is summed against `ref`, the
-// largest value seen so far (never below them, so nothing overflows).
-// Also clears `zero_n` ints at `zero_ptr` (barrier counters of the expansion
-// kernel that follows on the stream).
-// TWP: the weights dtype of a head projection carried by the launch (void: none)
-template <typename T, bool VEC, typename TWP = void>
-__global__ __launch_bounds__(kScanThreads) void scan_chunk_kernel(
-    const T *__restrict__ logits, ScanGeom g, float c, uint64_t *__restrict__ ckeys,
-    float2 *__restrict__ ctail, int32_t *__restrict__ cflag, int32_t *__restrict__ zero_ptr,
-    int zero_n, HeadProj hp) {
-  constexpr int EPL = Elem<T>::EPL;
-  constexpr int NL = Raw<T>::NL;
-  constexpr int STEP = kScanThreads * EPL;
-  constexpr float NINF = -__builtin_huge_valf();
-  __shared__ ScanLDS sh;
-  __shared__ uint64_t list[2][kMaxM];
-  __shared__ float wthr[kWaves];
-  if constexpr (!std::is_void<TWP>::value) {
-    if ((int)blockIdx.x >= g.nchunks) {
-      head_proj_tile<TWP>(hp, g.rows, blockIdx.y * hp.extra + blockIdx.x - g.nchunks,
-                          reinterpret_cast<float *>(sh.buf));
-      return;
-    }
-  }
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int row = blockIdx.y, seg = blockIdx.x;
-  const int M = g.M;
-  const int seg_start = seg * g.chunk;
-  const int seg_n = min(g.chunk, g.V - seg_start);
-  const int nbat = (seg_n + kScanChunk - 1) / kScanChunk;
-  const T *rowp = logits + (size_t)row * g.V + seg_start;
-  if (zero_ptr && blockIdx.x == 0 && blockIdx.y == 0)
-    for (int i = tid; i < zero_n; i += kScanThreads) zero_ptr[i] = 0;
-
-  Raw<T> ra, rb;
-  const __amdgpu_buffer_rsrc_t segr = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<T *>(rowp), 0, seg_n * (int)sizeof(T), 0x00020000);
-  auto load = [&](Raw<T> &r, int b) {
-    if constexpr (VEC)
-      load_batch_vec<T>(r, segr, b);
-    else
-      load_batch<T, false>(r, rowp + (size_t)b * kScanChunk, min(kScanChunk, seg_n - b * kScanChunk));
-  };
-  load(ra, 0);
-  if (tid == 0) sh.flag = 0;
-  for (int i = tid; i < M; i += kScanThreads) list[0][i] = 0ull;
-
-  int cur = 0, nl = 0;    // running list: list[cur][0..nl), sorted descending
-  float thr = NINF;       // after the first merge: only values above thr can enter
-  int wbase = 0;          // candidates of this wave since the last merge
-  Tail tail = sel::tail_empty();
-
-  // Merge the candidates in the regions (wc[r] keys each, all >= the list's
-  // threshold) into the running list; the keys that drop out join the tail.
-  auto merge_regions = [&](const int (&wc)[kWaves]) {
-    int nc = 0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) nc += wc[i];
-    if (nc == 0) return;
-    const uint64_t *L0 = list[cur];
-    uint64_t *L1 = list[cur ^ 1];
-    if (M <= 64) {
-      // In registers: every wave sorts its own region (chunks of 64, even waves
-      // descending, odd ones ascending), keeping its best 64; the four lists
-      // and then the running list meet in a tree (sel::merge_halves).  Every
-      // key that drops out joins this lane's tail.
-      static_assert(kWaves == 4, "merge tree of four waves");
-      const bool mydesc = (w & 1) == 0;
-      uint64_t *rg = sh.buf + w * kRegion;
-      const int n = wc[w];
-      uint64_t v = sel::wave_sort64(lane < n ? rg[lane] : 0ull, mydesc);
-      for (int c0 = 64; c0 < n; c0 += 64) {
-        const uint64_t ch = sel::wave_sort64(c0 + lane < n ? rg[c0 + lane] : 0ull, !mydesc);
-        v = mydesc ? sel::merge_halves(v, ch, true, tail, c) : sel::merge_halves(ch, v, false, tail, c);
-      }
-      if (w & 1) rg[lane] = v;  // (a wave only ever reads its own region before this)
-      __syncthreads();
-      if ((w & 1) == 0) {
-        v = sel::merge_halves(v, sh.buf[(w + 1) * kRegion + lane], w == 0, tail, c);
-        if (w == 2) rg[lane] = v;
-      }
-      __syncthreads();
-      if (w == 0) {
-        v = sel::merge_halves(v, sh.buf[2 * kRegion + lane], true, tail, c);
-        const int li = 63 - lane;  // the running list, reversed
-        v = sel::merge_halves(v, li < nl ? L0[li] : 0ull, true, tail, c);
-        if (lane >= M && v) sel::tail_add1(tail, key_value(v), c);
-        if (lane < M) L1[lane] = v;
-      }
-    } else {
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i)
-      if (tid == i && (wc[i] & 1)) sh.buf[i * kRegion + wc[i]] = 0ull;  // pad for paired reads
-    __syncthreads();
-    if (nc + nl <= 4 * kScanThreads) {
-      // a candidate's rank is the number of larger candidates (paired reads
-      // over the regions) plus the number of larger list keys (binary search);
-      // a list key's rank is its position plus the number of larger candidates
-      for (int it = tid; it < nc + nl; it += kScanThreads) {
-        uint64_t k;
-        int rank;
-        if (it < nc) {
-          int r = 0, o = it;
-#pragma unroll
-          for (int i = 0; i < kWaves - 1; ++i)
-            if (r == i && o >= wc[i]) {
-              o -= wc[i];
-              r = i + 1;
-            }
-          k = sh.buf[r * kRegion + o];
-          int lo = 0, hi = nl;
-          while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (L0[mid] > k)
-              lo = mid + 1;
-            else
-              hi = mid;
-          }
-          rank = lo;
-        } else {
-          rank = it - nc;
-          k = L0[rank];
-        }
-#pragma unroll
-        for (int r2 = 0; r2 < kWaves; ++r2) {
-          const ulonglong2 *p2 = reinterpret_cast<const ulonglong2 *>(sh.buf + r2 * kRegion);
-          const int np = (wc[r2] + 1) >> 1;
-#pragma unroll 4
-          for (int i = 0; i < np; ++i) {
-            const ulonglong2 kk = p2[i];
-            rank += (kk.x > k) + (kk.y > k);
-          }
-        }
-        if (rank < M)
-          L1[rank] = k;
-        else
-          sel::tail_add1(tail, key_value(k), c);
-      }
-    } else {
-      // many candidates: clear the unused part of every region, put the list
-      // keys into the free slots (the regions never fill past kRegionCap, so
-      // they fit), sort everything
-      for (int r = 0; r < kWaves; ++r)
-        for (int i = wc[r] + tid; i < kRegion; i += kScanThreads) sh.buf[r * kRegion + i] = 0ull;
-      __syncthreads();
-      for (int i = tid; i < nl; i += kScanThreads) {
-        int r = 0, o = i;
-#pragma unroll
-        for (int x = 0; x < kWaves - 1; ++x)
-          if (r == x && o >= kRegion - wc[x]) {
-            o -= kRegion - wc[x];
-            r = x + 1;
-          }
-        sh.buf[r * kRegion + wc[r] + o] = L0[i];
-      }
-      __syncthreads();
-      sel::block_sort_desc<kScanThreads>(sh.buf, kScanSortCap);
-      const int tot = nc + nl;
-      for (int i = M + tid; i < tot; i += kScanThreads) sel::tail_add1(tail, key_value(sh.buf[i]), c);
-      for (int i = tid; i < M; i += kScanThreads) L1[i] = i < tot ? sh.buf[i] : 0ull;
-    }
-    }
-    __syncthreads();
-    cur ^= 1;
-    nl = nc + nl < M ? nc + nl : M;
-  };
-
-  // after a merge: the threshold and the tail reference follow the list's M-th
-  // value (later tail elements lie at or below it)
-  auto after_merge = [&]() {
-    if (nl == M) thr = fmaxf(thr, key_value(list[cur][M - 1]));
-    if (thr > tail.m) {
-      tail.s *= sel::fast_exp2((tail.m - thr) * c);
-      tail.m = thr;
-    }
-    wbase = 0;
-  };
-
-  // one batch: b = batch index in the segment, raw = its registers.  The
-  // candidates accumulate in the regions; they are merged after the first
-  // batch (which sets the threshold), once about 2M have gathered (each merge
-  // raises the threshold), and at the end.
-  auto process = [&](Raw<T> &raw, int b) {
-    const int bstart = b * kScanChunk;
-    const int bn = min(kScanChunk, seg_n - bstart);
-    const bool first = b == 0;
-    if (VEC && bn < kScanChunk) pad_batch<T>(raw, bn);
-    // this thread's first element offset, opaque so that the per-element
-    // offsets are formed at each use rather than hoisted (40 registers)
-    int lb = tid * EPL;
-    asm volatile("" : "+v"(lb));
-    if (first) {
-      // every wave has >= q = ceil(M/4) lanes whose max is at least its q-th
-      // largest lane max, so at least M elements of the batch are >= the
-      // minimum over the waves: no top-M element lies below it.  The q-th
-      // largest is found bit by bit on order-preserving codes, one ballot per bit.
-      float tmax = NINF;
-#pragma unroll
-      for (int j = 0; j < NL; ++j)
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) tmax = fmaxf(tmax, elem<T>(raw, j, e));
-      const int q = (M + kWaves - 1) / kWaves;  // <= 64 since M <= 256
-      const uint32_t code = ordered_bits(tmax);
-      uint32_t pre = 0;
-#pragma unroll
-      for (int bit = 31; bit >= kLowBit<T>; --bit) {
-        const uint32_t cand = pre | (1u << bit);
-        if (__popcll(__ballot(code >= cand)) >= q) pre = cand;
-      }
-      pre = full_code<T>(pre);
-      if (lane == 0) wthr[w] = ordered_to_float(pre);
-      __syncthreads();
-      thr = wthr[0];
-#pragma unroll
-      for (int i = 1; i < kWaves; ++i) thr = fminf(thr, wthr[i]);
-      // (the tail's reference follows the threshold, at or above every element
-      // the tail takes, not the maximum: see the wave kernel)
-      tail.m = fmaxf(thr, -3.402823466e38f);
-    }
-    // Candidate test: the first batch keeps ties with its lower bound; later
-    // elements must beat the list's M-th value (they lose ties on the index).
-    // With a lower bound of -inf (fewer than M finite elements) the first
-    // batch keeps everything in range.
-    const float tb = thr;
-    const bool all_in = first && !(tb > NINF);
-    // One pass over the registers: the tail of the elements that cannot enter
-    // (against tail.m, which is >= all of them) and, for the rare elements that
-    // can, their key appended to this wave's region (wave-uniform branch on the
-    // comparison's lane mask; order (element, lane)).
-    fence_regs<T>(raw);
-    // one comparison x > te: te = tb for later batches; for the first batch
-    // any value below tb does (a few extra candidates are ranked exactly)
-    const float te = first && tb > NINF ? tb - (fabsf(tb) * 0x1p-20f + 0x1p-126f) : tb;
-    uint64_t *region = sh.buf + w * kRegion;
-    int wpos = wbase;  // wave-uniform
-    auto append = [&](bool pass, float x, int off) {
-      const uint64_t bal = __ballot(pass);
-      if (bal) {
-        const int at = wpos + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-        if (pass && at < kRegionCap) region[at] = make_key(x, (uint32_t)(seg_start + bstart + off));
-        wpos += __popcll(bal);
-      }
-    };
-    // exp((x - m) / tau) = 2^((x - m) c), 0 for candidates and padding.  While
-    // |m c| <= 128 the exponent is one fma, x c - (m c), off by at most half an
-    // ulp of m c (2^-17, the same for every term); otherwise two operations.
-    auto tail_pass = [&](auto expo) {
-      float s = 0.0f;
-#pragma unroll
-      for (int j = 0; j < NL; ++j)
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-          const float x = elem<T>(raw, j, e);
-          const bool pass = x > te;
-          s += sel::fast_exp2(pass ? NINF : expo(x));
-          append(pass, x, lb + j * STEP + e);
-        }
-      tail.s += s;
-    };
-    {
-      const float m = tail.m, mc = m * c;
-      if (fabsf(mc) <= 128.0f)
-        tail_pass([=](float x) { return __builtin_fmaf(x, c, -mc); });
-      else
-        tail_pass([=](float x) { return (x - m) * c; });
-    }
-    if (all_in) {
-      // a lower bound of -inf: the -inf elements in range are candidates too
-      // (read again from memory; the tail pass gave them nothing)
-#pragma unroll 1
-      for (int k = 0; k < NL * EPL; ++k) {
-        const int off = lb + (k / EPL) * STEP + k % EPL;
-        append(off < bn && to_f32<T>(rowp[bstart + off]) == NINF, NINF, off);
-      }
-    }
-    const int wn = wpos - wbase;
-    // the same candidate set, element by element (used by the fallback below)
-    auto is_cand = [&](float x, int off) { return x > te || (all_in && off < bn && x == NINF); };
-    const int wprev = wbase;
-    wbase += wn;
-    const int par = b & 1;
-    if (lane == 0) {
-      sh.wcnt[par][w] = wbase;
-      sh.wprev[par][w] = wprev;
-    }
-    __syncthreads();
-    int wc[kWaves], wp[kWaves];
-    bool overflow = false, crowded = false;
-    int ncand = 0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) {
-      wc[i] = sh.wcnt[par][i];
-      wp[i] = sh.wprev[par][i];
-      overflow |= wc[i] > kRegionCap;
-      crowded |= wc[i] > kRegionCap / 2;
-      ncand += wc[i];
-    }
-    if (!overflow) {
-      // a merge costs a fixed latency plus a term growing with the candidates
-      if (first || crowded || ncand >= kMergeAt * M || b == nbat - 1) {
-        merge_regions(wc);
-        after_merge();
-      }
-      return;
-    }
-    // a region overflowed (adversarial rows): merge what the earlier batches
-    // left, then stream this batch's candidates through the bounded selector,
-    // starting from the list
-    merge_regions(wp);
-    after_merge();
-    const uint64_t *L0 = list[cur];
-    uint64_t *L1 = list[cur ^ 1];
-    for (int i = tid; i < nl; i += kScanThreads) sh.buf[i] = L0[i];
-    if (tid == 0) {
-      sh.nbuf = nl;
-      sh.nlist = nl;
-      sh.thr = nl == M ? L0[M - 1] + 1 : 1ull;
-    }
-    __syncthreads();
-    // (the batch is read again from memory, one load group at a time)
-#pragma unroll 1
-    for (int j = 0; j < NL; ++j) {
-      uint64_t key[EPL];
-      float val[EPL];
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const int off = lb + j * STEP + e;
-        const float x = off < bn ? to_f32<T>(rowp[bstart + off]) : NINF;
-        const bool pass = is_cand(x, off);
-        key[e] = pass ? make_key(x, (uint32_t)(seg_start + bstart + off)) : 0ull;
-        val[e] = pass ? x : NINF;  // the non-candidates are already in the tail
-      }
-      stream_batch<EPL>(sh, key, val, M, tail, c);
-    }
-    if (sh.nbuf > sh.nlist) flush(sh, M, tail, c);
-    const int nn = sh.nlist;
-    for (int i = tid; i < M; i += kScanThreads) L1[i] = i < nn ? sh.buf[i] : 0ull;
-    __syncthreads();
-    cur ^= 1;
-    nl = nn;
-    after_merge();
-  };
-
-  // the next batch is always in flight while one is processed; VEC loads past
-  // the segment's end return zeros and cost no memory traffic
-  for (int b = 0; b < nbat; b += 2) {
-    if (VEC || b + 1 < nbat) load(rb, b + 1);
-    process(ra, b);
-    if (VEC || b + 2 < nbat) load(ra, b + 2);
-    if (b + 1 < nbat) process(rb, b + 1);
-  }
-
-  // a NaN makes a tail sum NaN (it never passes a comparison); +inf heads the list
-  if (!(tail.s == tail.s) || (nl && key_value(list[cur][0]) == __builtin_huge_valf()))
-    atomicOr(&sh.flag, 1);
-  const Tail t = sel::block_tail<kScanThreads>(tail, c, sh.red);
-  const size_t cidx = (size_t)row * g.nchunks + seg;
-  uint64_t *out = ckeys + cidx * M;
-  for (int i = tid; i < M; i += kScanThreads) out[i] = i < nl ? list[cur][i] : 0ull;
-  if (tid == 0) {
-    ctail[cidx] = make_float2(t.m, t.s);
-    cflag[cidx] = sh.flag ? DT_TREE_NONFINITE : 0;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Wave-streaming variant (M <= 64, rows read with 16-byte loads): the same
-// segments, batches and per-element work, but each wave keeps its own list of
-// its 64 best keys in registers (lane p: position p, descending) and merges
-// its own candidates into it when they gather -- no block barrier while the
-// segment streams, so a wave that merges does not hold up the other waves'
-// loads.  A candidate must beat a lower bound on the segment's M-th key:
-//   * the bound tb of the first two batches (as above, over the lane maxima of
-//     both; the one block barrier), ties kept.  Drawn from twice the elements,
-//     it admits about 40% fewer candidates over an eight-batch segment of
-//     Gaussian-like logits than the first batch's alone;
-//   * the wave's own list's M-th value, strictly: the wave's later elements
-//     have larger indices, so they lose ties with its own list.
-// Both depend on nothing but the data, so the candidates, the merges and the
-// order of every tail sum are the same from run to run.  (Reading the other
-// waves' list values as they stood was faster -- 40.2 against 43.3 us on 512
-// rows of 151936 bf16 logits -- but made the candidates, and with them the
-// tails' rounding, depend on timing; reading them two batches late, waiting
-// for them, gained nothing over the own bound.)
-// A wave merges once 48 candidates have gathered (fewer merges than at 32,
-// with the bound from two batches rising early enough).  The region holds
-// (index, value bits) pairs; the keys are formed in the merge.
-// The four wave lists meet once, at the end of the segment (two pairs side by
-// side, then the two results).  A wave whose
-// candidates overflow its region re-reads the batch and merges as it goes;
-// a first batch without a finite bound (mostly -inf or padding) takes every
-// element in range as a candidate that way.
-// Each wave keeps its next batch in flight in registers (two buffers; a third,
-// two batches ahead, measured slower: 43.2 against 40.0 us on 512 rows of
-// 151936 bf16 logits, with the bounds shared), four workgroups per CU.
-// ---------------------------------------------------------------------------
-template <typename T>
-struct WaveScan {
-  static constexpr int kBufs = 2;  // register batches per thread (2 or 3)
-  static constexpr int kRegion = 512;  // candidate keys a wave gathers between merges
-};
-
-// merge region[0..n) ((index << 32) | value bits each) into the wave's list
-// (descending keys, one per lane); keys that fall out of the best 64 join the
-// lane's tail.  fresh: the list is still empty, and the first 64 keys become
-// it sorted, with nothing to merge (wave-uniform; cleared here).
-__device__ inline void wave_merge(const uint64_t *region, int n, uint64_t &list, bool &fresh, Tail &tail,
-                                  float c) {
-  const int lane = threadIdx.x & 63;
-  for (int c0 = 0; c0 < n; c0 += 64) {
-    uint64_t k = 0ull;
-    if (c0 + lane < n) {
-      const uint64_t e = region[c0 + lane];
-      k = make_key(__uint_as_float((uint32_t)e), (uint32_t)(e >> 32));
-    }
-    const uint64_t srt = sel::wave_sort64(k, fresh);
-    list = fresh ? srt : sel::merge_halves(list, srt, true, tail, c);
-    fresh = false;
-  }
-}
+constexpr int kWaveRegion = 512;  // candidates a wave gathers between merges
 
 __device__ inline uint64_t readlane64(uint64_t v, int l) {
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
@@ -747,24 +251,105 @@ __device__ inline uint64_t readlane64(uint64_t v, int l) {
 // a value slightly below v (v finite): comparing x > below(v) keeps x == v
 __device__ inline float below(float v) { return v - (fabsf(v) * 0x1p-20f + 0x1p-126f); }
 
-template <typename T, typename TWP = void>
-__global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
+// a wave's list: entry r * 64 + lane, descending (0: empty)
+template <int R>
+struct WaveList {
+  uint64_t k[R];
+};
+
+// 64 ascending keys into the list; the 64 that drop out join the lanes' tails
+template <int R>
+__device__ inline void list_insert(WaveList<R> &l, uint64_t asc, Tail &tail, float c) {
+#pragma unroll
+  for (int r = 0; r < R - 1; ++r) {
+    const bool ga = l.k[r] > asc;
+    const uint64_t hi = ga ? l.k[r] : asc, lo = ga ? asc : l.k[r];
+    l.k[r] = sel::bitonic_clean64(hi, true);
+    asc = sel::bitonic_clean64(lo, false);
+  }
+  l.k[R - 1] = sel::merge_halves(l.k[R - 1], asc, true, tail, c);
+}
+
+// merge region[0..n) ((index << 32) | value bits each) into the wave's list.
+// fresh: the list is still empty, and the first 64 keys become its head sorted,
+// with nothing to merge (wave-uniform; cleared here).
+template <int R>
+__device__ inline void wave_merge(const uint64_t *region, int n, WaveList<R> &list, bool &fresh, Tail &tail,
+                                  float c) {
+  const int lane = threadIdx.x & 63;
+  for (int c0 = 0; c0 < n; c0 += 64) {
+    uint64_t k = 0ull;
+    if (c0 + lane < n) {
+      const uint64_t e = region[c0 + lane];
+      k = make_key(__uint_as_float((uint32_t)e), (uint32_t)(e >> 32));
+    }
+    const uint64_t srt = sel::wave_sort64(k, fresh);
+    if (fresh)
+      list.k[0] = srt;
+    else
+      list_insert<R>(list, srt, tail, c);
+    fresh = false;
+  }
+}
+
+// the list of another wave (in LDS, descending) into this wave's: the best 64 R
+// stay, the rest join the lanes' tails
+template <int R>
+__device__ inline void list_merge(WaveList<R> &l, const uint64_t *other, Tail &tail, float c) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint64_t o = other[R * 64 - 1 - (r * 64 + lane)];
+    const bool ga = l.k[r] > o;
+    const uint64_t lo = ga ? o : l.k[r];
+    l.k[r] = ga ? l.k[r] : o;
+    sel::tail_add1(tail, lo ? key_value(lo) : -__builtin_huge_valf(), c);
+  }
+  // (now bitonic over the 64 R entries)
+#pragma unroll
+  for (int h = R / 2; h > 0; h >>= 1)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((r & h) == 0) {
+        const uint64_t x = l.k[r], y = l.k[r + h];
+        l.k[r] = x > y ? x : y;
+        l.k[r + h] = x > y ? y : x;
+      }
+#pragma unroll
+  for (int r = 0; r < R; ++r) l.k[r] = sel::bitonic_clean64(l.k[r], true);
+}
+
+// the results of a row of one segment, written by the scan itself
+struct RowOut {
+  int32_t *ids;   // null: segment lists
+  float *vals, *tail;
+  int32_t *flag;
+  float inv_tau;
+};
+
+// K1: exact top-M of one segment (g.chunk elements from the row's 16-byte
+// boundary; the last one takes what is left) of one row, plus the tail of the
+// rest.  Also clears `zero_n` ints at `zero_ptr` (barrier counters of the
+// expansion kernel that follows on the stream).
+// R: list registers per lane; W: waves; TWP: the weights dtype of a head
+// projection carried by the launch (void: none)
+template <typename T, int R, int W, typename TWP = void>
+__global__ __launch_bounds__(W * 64) void scan_kernel(
     const T *__restrict__ logits, ScanGeom g, float c, uint64_t *__restrict__ ckeys,
     float2 *__restrict__ ctail, int32_t *__restrict__ cflag, int32_t *__restrict__ zero_ptr,
-    int zero_n, HeadProj hp) {
+    int zero_n, RowOut ro, HeadProj hp) {
   constexpr int EPL = Elem<T>::EPL;
   constexpr int NL = Raw<T>::NL;
-  constexpr int STEP = kScanThreads * EPL;
+  constexpr int STEP = W * 64 * EPL;
+  constexpr int BATCH = W * 64 * kScanPerThread;
   constexpr float NINF = -__builtin_huge_valf();
-  constexpr int kBufs = WaveScan<T>::kBufs;
-  constexpr int kWaveRegion = WaveScan<T>::kRegion;
-  __shared__ alignas(16) uint64_t regions[kWaves * kWaveRegion];
-  __shared__ uint64_t wl[kWaves][64];
-  __shared__ float wthr[kWaves];
-  __shared__ float2 red[kWaves];
+  __shared__ alignas(16) uint64_t regions[W * kWaveRegion];
+  __shared__ uint64_t wl[W][R * 64];
+  __shared__ float wthr[W];
+  __shared__ float2 red[W];
   __shared__ int flag;
-  static_assert(kWaves * kWaveRegion * 8 >= kWaves * 256 * 4, "projection partials fit the regions");
   if constexpr (!std::is_void<TWP>::value) {
+    static_assert(W == kProjWaves && W * kWaveRegion * 8 >= W * 256 * 4, "projection partials fit the regions");
     if ((int)blockIdx.x >= g.nchunks) {
       head_proj_tile<TWP>(hp, g.rows, blockIdx.y * hp.extra + blockIdx.x - g.nchunks,
                           reinterpret_cast<float *>(regions));
@@ -774,45 +359,45 @@ __global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int row = blockIdx.y, seg = blockIdx.x;
   const int M = g.M;
-  const int seg_start = seg * g.chunk;
-  const int seg_n = min(g.chunk, g.V - seg_start);
-  const int nbat = (seg_n + kScanChunk - 1) / kScanChunk;
-  const T *rowp = logits + (size_t)row * g.V + seg_start;
+  // the row from the 16-byte boundary at or below its start: `mis` elements early
+  const T *rowp = logits + (size_t)row * g.V;
+  const int mis = (int)((reinterpret_cast<uintptr_t>(rowp) & 15) / sizeof(T));
+  const int seg_lo = seg * g.chunk;
+  const int seg_n = (seg == g.nchunks - 1 ? g.V + mis : seg_lo + g.chunk) - seg_lo;
+  const int seg_start = seg_lo - mis;  // row index of the segment's element 0
+  const int nbat = (seg_n + BATCH - 1) / BATCH;
+  const int lo0 = seg == 0 ? mis : 0;  // elements of its first batch before the row
+  const T *segp = rowp + seg_start;
   if (zero_ptr && blockIdx.x == 0 && blockIdx.y == 0)
-    for (int i = tid; i < zero_n; i += kScanThreads) zero_ptr[i] = 0;
+    for (int i = tid; i < zero_n; i += W * 64) zero_ptr[i] = 0;
   const __amdgpu_buffer_rsrc_t segr = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<T *>(rowp), 0, seg_n * (int)sizeof(T), 0x00020000);
-  // loads past the segment's end return zeros (no traffic); pad_batch makes them -inf
+      const_cast<T *>(segp), 0, (seg_n * (int)sizeof(T) + 15) & ~15, 0x00020000);
   int lb = tid * EPL;
   asm volatile("" : "+v"(lb));
-  Raw<T> ra, rb, rc;
+  Raw<T> ra, rb;
   const bool two = nbat > 1;
-  load_batch_vec<T>(ra, segr, 0);
-  if (two) load_batch_vec<T>(rb, segr, 1);
+  load_batch<T, W>(ra, segr, 0);
+  if (two) load_batch<T, W>(rb, segr, 1);
   if (tid == 0) flag = 0;
 
-  // ---- the first two batches' lower bound tb (every wave: the ceil(M/4)-th
-  // largest of its lane maxima; the minimum over the waves).
-  // (Two batches rather than one: the bound then admits about 40% fewer
-  // candidates over a segment of eight batches, and every candidate costs an
-  // append and a share of a merge.)
-  const int bn0 = min(kScanChunk, seg_n);
-  if (bn0 < kScanChunk) pad_batch<T>(ra, bn0);
+  // ---- the first two batches' lower bound tb -----------------------------------
+  const int bn0 = min(BATCH, seg_n);
+  if (bn0 < BATCH || lo0 > 0) pad_batch<T, W>(ra, lo0, bn0);
   float tmax = NINF;
 #pragma unroll
   for (int j = 0; j < NL; ++j)
 #pragma unroll
     for (int e = 0; e < EPL; ++e) tmax = fmaxf(tmax, elem<T>(ra, j, e));
   if (two) {
-    const int bn1 = min(kScanChunk, seg_n - kScanChunk);
-    if (bn1 < kScanChunk) pad_batch<T>(rb, bn1);
+    const int bn1 = min(BATCH, seg_n - BATCH);
+    if (bn1 < BATCH) pad_batch<T, W>(rb, 0, bn1);
 #pragma unroll
     for (int j = 0; j < NL; ++j)
 #pragma unroll
       for (int e = 0; e < EPL; ++e) tmax = fmaxf(tmax, elem<T>(rb, j, e));
   }
   {
-    const int q = (M + kWaves - 1) / kWaves;
+    const int q = (M + W - 1) / W;  // <= 64 since M <= 256 and W >= 4
     const uint32_t code = ordered_bits(tmax);
     uint32_t pre = 0;
 #pragma unroll
@@ -824,11 +409,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
     if (lane == 0) wthr[w] = ordered_to_float(pre);
   }
   __syncthreads();
-  // the batch after them (issued after the barrier, which would wait for it)
-  if constexpr (kBufs == 3) load_batch_vec<T>(rc, segr, 2);
   float tb = wthr[0];
 #pragma unroll
-  for (int i = 1; i < kWaves; ++i) tb = fminf(tb, wthr[i]);
+  for (int i = 1; i < W; ++i) tb = fminf(tb, wthr[i]);
   const bool all_in = !(tb > NINF);
   const float tlow = all_in ? NINF : below(tb);
   // The tail's reference follows the bound, which every element the tail
@@ -838,31 +421,34 @@ __global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
   Tail tail = sel::tail_empty();
   tail.m = fmaxf(tlow, -3.402823466e38f);
 
-  uint64_t list = 0ull;   // this wave's best keys (0: empty)
+  WaveList<R> list;       // this wave's best keys
+#pragma unroll
+  for (int r = 0; r < R; ++r) list.k[r] = 0ull;
   bool fresh = true;      // no merge yet (the list is empty)
   float v_own = NINF;     // its M-th value once it holds M keys
   int wpos = 0;           // candidates in the region (wave-uniform)
-  const int kMergeTrig = M < 16 ? 2 * M : 48;
+  const int kMergeTrig = R > 1 ? 64 : (M < 16 ? 2 * M : 48);
   uint64_t *region = regions + w * kWaveRegion;
 
-  auto after_merge = [&]() {
-    const uint64_t km = readlane64(list, M - 1);
-    if (km) v_own = key_value(km);
-  };
   auto merge_now = [&]() {
-    wave_merge(region, wpos, list, fresh, tail, c);
+    wave_merge<R>(region, wpos, list, fresh, tail, c);
     wpos = 0;
-    after_merge();
+    uint64_t km = 0ull;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r == (M - 1) >> 6) km = readlane64(list.k[r], (M - 1) & 63);
+    if (km) v_own = key_value(km);
   };
   // the candidates of batch b read again from memory, merged whenever the
   // region might overflow (the tail already holds the batch's other elements)
-  auto slow = [&](int bstart, int bn, float te, bool in_all) {
+  auto slow = [&](int bstart, int lo, int bn, float te, bool in_all) {
 #pragma unroll 1
     for (int k = 0; k < NL * EPL; ++k) {
       const int off = lb + (k / EPL) * STEP + k % EPL;
-      const float x = off < bn ? to_f32<T>(rowp[bstart + off]) : NINF;
-      const bool pass = off < bn && (x > te || (in_all && x == NINF));
-      if (in_all && off < bn && x != x) tail.s = x;  // (a NaN: the row is flagged)
+      const bool in = off >= lo && off < bn;
+      const float x = in ? to_f32<T>(segp[bstart + off]) : NINF;
+      const bool pass = in && (x > te || (in_all && x == NINF));
+      if (in_all && in && x != x) tail.s = x;  // (a NaN: the row is flagged)
       const uint64_t bal = __ballot(pass);
       if (bal) {
         if (wpos + 64 > kWaveRegion) merge_now();
@@ -876,9 +462,10 @@ __global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
   };
 
   auto process = [&](Raw<T> &raw, int b) {
-    const int bstart = b * kScanChunk;
-    const int bn = min(kScanChunk, seg_n - bstart);
-    if (b > 0 && bn < kScanChunk) pad_batch<T>(raw, bn);
+    const int bstart = b * BATCH;
+    const int bn = min(BATCH, seg_n - bstart);
+    const int lo = b == 0 ? lo0 : 0;
+    if (b > 0 && bn < BATCH) pad_batch<T, W>(raw, 0, bn);
     // this batch's bound
     float te = tlow;
     if (b > 0) te = fmaxf(te, v_own);
@@ -888,13 +475,15 @@ __global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
       tail.m = te;
     }
     if (b == 0 && all_in) {
-      slow(bstart, bn, NINF, true);
+      slow(bstart, lo, bn, NINF, true);
     } else {
       fence_regs<T>(raw);
       const int wprev = wpos;
       const int ibase = seg_start + bstart + lb;  // row index of this thread's element (0, 0)
       // exp((x - m) / tau) = 2^((x - m) c) for every element; a candidate (x >
-      // te, rare) is appended to the region and adds nothing
+      // te, rare) is appended to the region and adds nothing.  While |m c| <= 128
+      // the exponent is one fma, x c - (m c), off by at most half an ulp of m c
+      // (2^-17, the same for every term); otherwise two operations.
       auto tail_pass = [&](auto expo) {
         float s = 0.0f;
 #pragma unroll
@@ -931,53 +520,65 @@ __global__ __launch_bounds__(kScanThreads) void scan_wave_kernel(
         // overflow: merge what came before, then this batch's candidates again
         wpos = wprev;
         if (wpos) merge_now();
-        slow(bstart, bn, te, false);
+        slow(bstart, lo, bn, te, false);
       }
     }
     if (wpos >= kMergeTrig || (wpos && b == nbat - 1)) merge_now();
   };
 
-  // a buffer is refilled with the batch kBufs ahead as soon as it is processed
-  // (loads past the segment's end return zeros and cost no traffic)
-  for (int b = 0; b < nbat; b += kBufs) {
+  // a buffer is refilled with the batch two ahead as soon as it is processed
+  // (loads past the segment's end return zeros and cost no traffic; a third
+  // buffer measured slower: 43.2 against 40.0 us on 512 rows of 151936 bf16)
+  for (int b = 0; b < nbat; b += 2) {
     process(ra, b);
-    if (b + kBufs < nbat) load_batch_vec<T>(ra, segr, b + kBufs);
+    if (b + 2 < nbat) load_batch<T, W>(ra, segr, b + 2);
     if (b + 1 < nbat) {
       process(rb, b + 1);
-      if (b + 1 + kBufs < nbat) load_batch_vec<T>(rb, segr, b + 1 + kBufs);
-    }
-    if constexpr (kBufs == 3) {
-      if (b + 2 < nbat) {
-        process(rc, b + 2);
-        if (b + 2 + kBufs < nbat) load_batch_vec<T>(rc, segr, b + 2 + kBufs);
-      }
+      if (b + 3 < nbat) load_batch<T, W>(rb, segr, b + 3);
     }
   }
 
-  // ---- the four wave lists meet: the segment's M best, the rest to the tail
-  // (waves 0 and 2 merge the pairs side by side, wave 2's result ascending;
-  // wave 0 merges the two)
-  wl[w][lane] = list;
-  __syncthreads();
+  // ---- the wave lists meet, pairs side by side: the segment's M best, the rest
+  // to the tail
+#pragma unroll
+  for (int s = 1; s < W; s <<= 1) {
+    if ((w & (2 * s - 1)) == s)
+#pragma unroll
+      for (int r = 0; r < R; ++r) wl[w][r * 64 + lane] = list.k[r];
+    __syncthreads();
+    if ((w & (2 * s - 1)) == 0) list_merge<R>(list, wl[w + s], tail, c);
+  }
   const size_t cidx = (size_t)row * g.nchunks + seg;
-  if ((w & 1) == 0) wl[w][lane] = sel::merge_halves(wl[w][lane], wl[w + 1][63 - lane], w == 0, tail, c);
-  __syncthreads();
   if (w == 0) {
-    uint64_t f = sel::merge_halves(wl[0][lane], wl[2][lane], true, tail, c);
-    if (lane >= M) {
-      if (f) sel::tail_add1(tail, key_value(f), c);
-      f = 0ull;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int p = r * 64 + lane;
+      uint64_t f = list.k[r];
+      if (p >= M) {
+        if (f) sel::tail_add1(tail, key_value(f), c);
+        f = 0ull;
+      } else if (ro.ids) {
+        ro.ids[(size_t)row * M + p] = f ? (int32_t)key_index(f) : -1;
+        ro.vals[(size_t)row * M + p] = f ? key_value(f) : NINF;
+      } else {
+        ckeys[cidx * M + p] = f;
+      }
+      // +inf heads the list
+      if (r == 0 && lane == 0 && f && key_value(f) == __builtin_huge_valf()) atomicOr(&flag, 1);
     }
-    if (lane < M) ckeys[cidx * M + lane] = f;
-    // +inf heads the list
-    if (lane == 0 && f && key_value(f) == __builtin_huge_valf()) atomicOr(&flag, 1);
   }
   // a NaN makes a tail sum NaN (it never passes a comparison)
   if (!(tail.s == tail.s)) atomicOr(&flag, 1);
-  const Tail t = sel::block_tail<kScanThreads>(tail, c, red);
+  const Tail t = sel::block_tail<W * 64>(tail, c, red);
   if (tid == 0) {
-    ctail[cidx] = make_float2(t.m, t.s);
-    cflag[cidx] = flag ? DT_TREE_NONFINITE : 0;
+    const int fl = flag ? DT_TREE_NONFINITE : 0;
+    if (ro.ids) {
+      ro.tail[row] = t.s > 0.0f ? t.m * ro.inv_tau + logf(t.s) : NINF;
+      ro.flag[row] = fl;
+    } else {
+      ctail[cidx] = make_float2(t.m, t.s);
+      cflag[cidx] = fl;
+    }
   }
 }
 
@@ -988,7 +589,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_merge_kernel(
     const float2 *__restrict__ ctail, const int32_t *__restrict__ cflag, int32_t *__restrict__ cand,
     float *__restrict__ candv, float *__restrict__ tailR, int32_t *__restrict__ rflag) {
   extern __shared__ uint64_t sortbuf[];  // merge_buf_bytes(nchunks, M)
-  __shared__ float2 red[kWaves];
+  __shared__ float2 red[kScanThreads / 64];
   __shared__ int flag;
   const int row = blockIdx.x;
   sel::merge_row<kScanThreads, false, SHIFT>(ckeys + (size_t)row * g.nchunks * g.M, g.nchunks, g.M,
@@ -1064,38 +665,25 @@ static void launch_maybe_timed(F kernel, dim3 grid, dim3 block, uint32_t lds, hi
     hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
 }
 
-template <typename T, bool VEC>
+template <typename T, int R, int W, typename TWP>
+static void launch_scan_k(const T *p, const ScanGeom &g, float c, const Workspace &ws, int32_t *zero_ptr,
+                          int zero_n, const RowOut &ro, const HeadProj *hp, hipStream_t s, hipEvent_t t0,
+                          hipEvent_t t1) {
+  launch_maybe_timed(scan_kernel<T, R, W, TWP>, dim3(g.nchunks + (hp ? hp->extra : 0), g.rows), dim3(W * 64), 0, s,
+                     t0, t1, p, g, c, ws.chunk_keys, ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, ro,
+                     hp ? *hp : HeadProj{});
+}
+
+template <typename T, int R>
 static void launch_scan_t(const T *p, const ScanGeom &g, float c, const Workspace &ws, int32_t *zero_ptr,
-                          int zero_n, const HeadProj *hp, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
-  const dim3 block(kScanThreads);
-  if (VEC && g.M <= 64) {
-    // the wave-streaming kernel
-    if (!hp) {
-      launch_maybe_timed(scan_wave_kernel<T>, dim3(g.nchunks, g.rows), block, 0, s, t0, t1, p, g, c,
-                         ws.chunk_keys, ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, HeadProj{});
-      return;
-    }
-    const dim3 grid(g.nchunks + hp->extra, g.rows);
-    if (hp->wdt == DT_BF16)
-      launch_maybe_timed(scan_wave_kernel<T, uint16_t>, grid, block, 0, s, t0, t1, p, g, c, ws.chunk_keys,
-                         ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, *hp);
-    else
-      launch_maybe_timed(scan_wave_kernel<T, float>, grid, block, 0, s, t0, t1, p, g, c, ws.chunk_keys,
-                         ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, *hp);
-    return;
-  }
-  if (!hp) {
-    launch_maybe_timed(scan_chunk_kernel<T, VEC>, dim3(g.nchunks, g.rows), block, 0, s, t0, t1, p, g, c,
-                       ws.chunk_keys, ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, HeadProj{});
-    return;
-  }
-  const dim3 grid(g.nchunks + hp->extra, g.rows);
-  if (hp->wdt == DT_BF16)
-    launch_maybe_timed(scan_chunk_kernel<T, VEC, uint16_t>, grid, block, 0, s, t0, t1, p, g, c, ws.chunk_keys,
-                       ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, *hp);
+                          int zero_n, const RowOut &ro, const HeadProj *hp, hipStream_t s, hipEvent_t t0,
+                          hipEvent_t t1) {
+  if (hp && hp->wdt == DT_BF16)
+    launch_scan_k<T, R, 4, uint16_t>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
+  else if (hp)
+    launch_scan_k<T, R, 4, float>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
   else
-    launch_maybe_timed(scan_chunk_kernel<T, VEC, float>, grid, block, 0, s, t0, t1, p, g, c, ws.chunk_keys,
-                       ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, *hp);
+    launch_scan_k<T, R, 4, void>(p, g, c, ws, zero_ptr, zero_n, ro, nullptr, s, t0, t1);
 }
 
 HeadProj head_proj_args(const dt_plan *p, int rows, const void *H, const dt_domino_head &hd, float *a_out) {
@@ -1112,24 +700,30 @@ HeadProj head_proj_args(const dt_plan *p, int rows, const void *H, const dt_domi
   return h;
 }
 
+// One kernel for every row address, row length and M: the register list grows
+// with M (one register per lane for each 64).  A kernel of its own per block for
+// M > 64, reading rows that are not 16-byte aligned element by element, took
+// 64.6 us for 128 rows of 151937 bf16 at M = 128 (dt_scan_topm with it 89.6 us,
+// with this one 42.7); aligned rows at M = 64 run as before (512 rows of 151936
+// bf16: 39 us).  direct: rows of one segment give their results here.
 hipError_t launch_scan_chunks(const void *logits, int ldt, const ScanGeom &g, float inv_tau,
                               const Workspace &ws, int32_t *zero_ptr, int zero_n, hipStream_t s,
-                              hipEvent_t t0, hipEvent_t t1, const HeadProj *hp) {
+                              hipEvent_t t0, hipEvent_t t1, const HeadProj *hp, bool direct) {
   const float c = 1.4426950408889634f * inv_tau;  // exp(x / tau) = exp2(x * c)
-  const bool aligned = (reinterpret_cast<uintptr_t>(logits) % 16) == 0;
-  if (ldt == DT_BF16) {
-    const uint16_t *p = static_cast<const uint16_t *>(logits);
-    if (aligned && g.V % 8 == 0)
-      launch_scan_t<uint16_t, true>(p, g, c, ws, zero_ptr, zero_n, hp, s, t0, t1);
+  const RowOut ro = direct ? RowOut{ws.cand, ws.candv, ws.tail, ws.row_flag, inv_tau}
+                           : RowOut{nullptr, nullptr, nullptr, nullptr, 0.0f};
+  auto launch = [&](auto *p) {
+    if (g.M <= 64)
+      launch_scan_t<std::remove_cv_t<std::remove_pointer_t<decltype(p)>>, 1>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
+    else if (g.M <= 128)
+      launch_scan_t<std::remove_cv_t<std::remove_pointer_t<decltype(p)>>, 2>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
     else
-      launch_scan_t<uint16_t, false>(p, g, c, ws, zero_ptr, zero_n, hp, s, t0, t1);
-  } else {
-    const float *p = static_cast<const float *>(logits);
-    if (aligned && g.V % 4 == 0)
-      launch_scan_t<float, true>(p, g, c, ws, zero_ptr, zero_n, hp, s, t0, t1);
-    else
-      launch_scan_t<float, false>(p, g, c, ws, zero_ptr, zero_n, hp, s, t0, t1);
-  }
+      launch_scan_t<std::remove_cv_t<std::remove_pointer_t<decltype(p)>>, 4>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
+  };
+  if (ldt == DT_BF16)
+    launch(static_cast<const uint16_t *>(logits));
+  else
+    launch(static_cast<const float *>(logits));
   return hipGetLastError();
 }
 

@@ -207,3 +207,32 @@ def test_scan_signed_zeros(dtype):
     xd = synth.f32_to_bf16_bits(x) if dtype == synth.DT_BF16 else x
     _check(xd, dtype, 64, 1.0, case=f"signed zeros {dtype}")
     _check(xd, dtype, 200, 0.5, case=f"signed zeros M=200 {dtype}")
+
+
+@pytest.mark.parametrize("dtype,per", [(synth.DT_BF16, 8), (synth.DT_F32, 4)], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("M", [1, 64, 65, 128, 129, 256])
+def test_scan_rows_at_any_offset(dtype, per, M):
+    # rows that begin at every element of a 16-byte granule, of lengths just around
+    # whole batches and granules and below one granule, between NaNs that no row may
+    # read: the same ids and values as the oracle, and the tail within its rounding
+    base = synth.peaked_logits(11, 0, 4, 3 * 10240 + 16, dtype, 1, 4, 6.0, 12.0)
+    for off, V in [(0, 10240), (1, 10239), (per - 1, 10241), (3, 20480 + per - 1), (2, 257),
+                   (1, max(M, per - 1)), (per // 2, 30720 + 1)]:
+        if V < M:
+            continue
+        rows = np.ascontiguousarray(base[:3, :V])
+        x = to_dev(rows, dtype)
+        buf = torch.full((x.numel() + 2 * per,), float("nan"), dtype=x.dtype, device=x.device)
+        view = buf[off:off + x.numel()].view(3, V)
+        view.copy_(x)
+        print(f"[scan] offset {off} V={V} M={M} dtype={dtype}", flush=True)
+        ids, vals, tail, flags = (a.cpu().numpy() for a in binding.scan_topm(view, M, 0.7))
+        X = oracle.widen(rows, dtype)
+        assert not flags.any(), (off, V)
+        for r in range(3):
+            rid, rx, rR = oracle.scan_row(X[r], M, oracle.effective_temperature(0.7))
+            np.testing.assert_array_equal(ids[r], rid, err_msg=f"offset {off} V {V} row {r}")
+            np.testing.assert_array_equal(vals[r].astype(np.float64), rx)
+            # fp32 sums of V terms over 256 threads and a tree: (V / 256 + 16) roundings of 2^-24,
+            # each term exact to a few ulps of its exponent
+            assert tail[r] == rR or abs(tail[r] - rR) <= (V / 256 + 64) * 2.0 ** -24 * max(1.0, abs(rR)), (off, V, r)
