@@ -178,8 +178,9 @@ __host__ __device__ inline Lds lds_layout(int dh, int G, int M, int nchunks, int
   l.Sn = take(CH * UW * 4);
   l.ell = take(CH * MP * 4);
   l.rnk = take(CH * MP * 2);
-  // merge_row's buffer, or merge_row_tree's (NT keys)
-  const int sortb = sel::merge_buf_bytes(nchunks, M) > NT * 8 ? sel::merge_buf_bytes(nchunks, M) : NT * 8;
+  // the row merges' LDS: NT keys per 64 slots of the menu
+  const int need = NT * 8 * (M > 128 ? 4 : (M > 64 ? 2 : 1));
+  const int sortb = sel::merge_buf_bytes(nchunks, M) > need ? sel::merge_buf_bytes(nchunks, M) : need;
   l.sortbuf = reuse;
   if (reuse + sortb > o) o = reuse + sortb;
   l.total = o;
@@ -642,14 +643,21 @@ __global__ __launch_bounds__(NT) void expand_kernel(ExpArgs a) {
                                 a.tailR + row, a.rflag + row, a.c_all);
     }
   } else {
-    for (int d = member; d < L; d += G) {
-      const int row = t * L + d;
-      sel::merge_row<NT, true, true>(a.ckeys + (size_t)row * a.nchunks * M, a.nchunks, M,
-                               a.ctail + (size_t)row * a.nchunks, a.cflag + (size_t)row * a.nchunks,
-                               a.c2, a.inv_tau, sortbuf, red, &scal[S_MERGEFLAG],
-                               a.cand + (size_t)row * M, a.candv + (size_t)row * M, a.tailR + row,
-                               a.rflag + row, a.c_all);
-    }
+    auto rows = [&](auto regs) {
+      for (int d = member; d < L; d += G) {
+        const int row = t * L + d;
+        sel::merge_row_lists<true, NT, decltype(regs)::value, true>(
+            a.ckeys + (size_t)row * a.nchunks * M, a.nchunks, M, a.ctail + (size_t)row * a.nchunks,
+            a.cflag + (size_t)row * a.nchunks, a.c2, a.inv_tau, sortbuf, red, &scal[S_MERGEFLAG],
+            a.cand + (size_t)row * M, a.candv + (size_t)row * M, a.tailR + row, a.rflag + row, a.c_all);
+      }
+    };
+    if (M <= 64)
+      rows(std::integral_constant<int, 1>{});
+    else if (M <= 128)
+      rows(std::integral_constant<int, 2>{});
+    else
+      rows(std::integral_constant<int, 4>{});
   }
   {
     // the root's path state (h0 or zeros) in slot ecap-1: this member's units

@@ -41,7 +41,7 @@
 // loads stay on pages that hold the row.  (Reading such rows element by element
 // took 64.6 us for 128 rows of 151937 bf16 at M = 128; see launch_scan_chunks.)
 //
-// The per-row merge of the segment lists (merge_row and its register variants)
+// The per-row merge of the segment lists (merge_row_lists and its variants)
 // runs inside the expansion kernels, or in a small kernel of its own for
 // dt_scan_topm; a row of one segment needs none there (its list is the result).
 //
@@ -251,30 +251,11 @@ __device__ inline uint64_t readlane64(uint64_t v, int l) {
 // a value slightly below v (v finite): comparing x > below(v) keeps x == v
 __device__ inline float below(float v) { return v - (fabsf(v) * 0x1p-20f + 0x1p-126f); }
 
-// a wave's list: entry r * 64 + lane, descending (0: empty)
-template <int R>
-struct WaveList {
-  uint64_t k[R];
-};
-
-// 64 ascending keys into the list; the 64 that drop out join the lanes' tails
-template <int R>
-__device__ inline void list_insert(WaveList<R> &l, uint64_t asc, Tail &tail, float c) {
-#pragma unroll
-  for (int r = 0; r < R - 1; ++r) {
-    const bool ga = l.k[r] > asc;
-    const uint64_t hi = ga ? l.k[r] : asc, lo = ga ? asc : l.k[r];
-    l.k[r] = sel::bitonic_clean64(hi, true);
-    asc = sel::bitonic_clean64(lo, false);
-  }
-  l.k[R - 1] = sel::merge_halves(l.k[R - 1], asc, true, tail, c);
-}
-
 // merge region[0..n) ((index << 32) | value bits each) into the wave's list.
 // fresh: the list is still empty, and the first 64 keys become its head sorted,
 // with nothing to merge (wave-uniform; cleared here).
 template <int R>
-__device__ inline void wave_merge(const uint64_t *region, int n, WaveList<R> &list, bool &fresh, Tail &tail,
+__device__ inline void wave_merge(const uint64_t *region, int n, sel::WaveList<R> &list, bool &fresh, Tail &tail,
                                   float c) {
   const int lane = threadIdx.x & 63;
   for (int c0 = 0; c0 < n; c0 += 64) {
@@ -287,36 +268,9 @@ __device__ inline void wave_merge(const uint64_t *region, int n, WaveList<R> &li
     if (fresh)
       list.k[0] = srt;
     else
-      list_insert<R>(list, srt, tail, c);
+      sel::list_insert<R>(list, srt, tail, c);
     fresh = false;
   }
-}
-
-// the list of another wave (in LDS, descending) into this wave's: the best 64 R
-// stay, the rest join the lanes' tails
-template <int R>
-__device__ inline void list_merge(WaveList<R> &l, const uint64_t *other, Tail &tail, float c) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint64_t o = other[R * 64 - 1 - (r * 64 + lane)];
-    const bool ga = l.k[r] > o;
-    const uint64_t lo = ga ? o : l.k[r];
-    l.k[r] = ga ? l.k[r] : o;
-    sel::tail_add1(tail, lo ? key_value(lo) : -__builtin_huge_valf(), c);
-  }
-  // (now bitonic over the 64 R entries)
-#pragma unroll
-  for (int h = R / 2; h > 0; h >>= 1)
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if ((r & h) == 0) {
-        const uint64_t x = l.k[r], y = l.k[r + h];
-        l.k[r] = x > y ? x : y;
-        l.k[r + h] = x > y ? y : x;
-      }
-#pragma unroll
-  for (int r = 0; r < R; ++r) l.k[r] = sel::bitonic_clean64(l.k[r], true);
 }
 
 // the results of a row of one segment, written by the scan itself
@@ -421,7 +375,7 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
   Tail tail = sel::tail_empty();
   tail.m = fmaxf(tlow, -3.402823466e38f);
 
-  WaveList<R> list;       // this wave's best keys
+  sel::WaveList<R> list;       // this wave's best keys
 #pragma unroll
   for (int r = 0; r < R; ++r) list.k[r] = 0ull;
   bool fresh = true;      // no merge yet (the list is empty)
@@ -546,7 +500,7 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
 #pragma unroll
       for (int r = 0; r < R; ++r) wl[w][r * 64 + lane] = list.k[r];
     __syncthreads();
-    if ((w & (2 * s - 1)) == 0) list_merge<R>(list, wl[w + s], tail, c);
+    if ((w & (2 * s - 1)) == 0) sel::list_merge<R>(list, [&](int i) { return wl[w + s][i]; }, tail, c);
   }
   const size_t cidx = (size_t)row * g.nchunks + seg;
   if (w == 0) {
@@ -583,20 +537,19 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
 }
 
 // K2 (dt_scan_topm and one-shot calls): merge the chunk lists of one row
-template <bool SHIFT>
+template <int R, bool SHIFT>
 __global__ __launch_bounds__(kScanThreads) void scan_merge_kernel(
     ScanGeom g, float c, float inv_tau, const uint64_t *__restrict__ ckeys,
     const float2 *__restrict__ ctail, const int32_t *__restrict__ cflag, int32_t *__restrict__ cand,
     float *__restrict__ candv, float *__restrict__ tailR, int32_t *__restrict__ rflag) {
-  extern __shared__ uint64_t sortbuf[];  // merge_buf_bytes(nchunks, M)
+  __shared__ uint64_t xbuf[kScanThreads * R];
   __shared__ float2 red[kScanThreads / 64];
   __shared__ int flag;
   const int row = blockIdx.x;
-  sel::merge_row<kScanThreads, false, SHIFT>(ckeys + (size_t)row * g.nchunks * g.M, g.nchunks, g.M,
-                                      ctail + (size_t)row * g.nchunks, cflag + (size_t)row * g.nchunks,
-                                      c, inv_tau, sortbuf, red, &flag, cand + (size_t)row * g.M,
-                                      candv + (size_t)row * g.M, tailR + row, rflag + row,
-                                      nullptr);
+  sel::merge_row_lists<false, kScanThreads, R, SHIFT>(
+      ckeys + (size_t)row * g.nchunks * g.M, g.nchunks, g.M, ctail + (size_t)row * g.nchunks,
+      cflag + (size_t)row * g.nchunks, c, inv_tau, xbuf, red, &flag, cand + (size_t)row * g.M,
+      candv + (size_t)row * g.M, tailR + row, rflag + row, nullptr);
 }
 
 }  // namespace
@@ -703,8 +656,8 @@ HeadProj head_proj_args(const dt_plan *p, int rows, const void *H, const dt_domi
 // One kernel for every row address, row length and M: the register list grows
 // with M (one register per lane for each 64).  A kernel of its own per block for
 // M > 64, reading rows that are not 16-byte aligned element by element, took
-// 64.6 us for 128 rows of 151937 bf16 at M = 128 (dt_scan_topm with it 89.6 us,
-// with this one 42.7); aligned rows at M = 64 run as before (512 rows of 151936
+// 64.6 us for 128 rows of 151937 bf16 at M = 128, this one 19.8 (with the rows'
+// merge, dt_scan_topm 87.7 -> 23.6 us); aligned rows at M = 64 run as before (512 rows of 151936
 // bf16: 39 us).  direct: rows of one segment give their results here.
 hipError_t launch_scan_chunks(const void *logits, int ldt, const ScanGeom &g, float inv_tau,
                               const Workspace &ws, int32_t *zero_ptr, int zero_n, hipStream_t s,
@@ -729,13 +682,11 @@ hipError_t launch_scan_chunks(const void *logits, int ldt, const ScanGeom &g, fl
 
 hipError_t launch_scan_merge(const ScanGeom &g, float inv_tau, const Workspace &ws, hipStream_t s, bool shift) {
   const float c = 1.4426950408889634f * inv_tau;
-  const size_t lds = merge_lds_bytes(g);
-  const auto kernel = shift ? scan_merge_kernel<true> : scan_merge_kernel<false>;
-  hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(g.rows), dim3(kScanThreads), lds, s, g, c, inv_tau,
-                     ws.chunk_keys, ws.chunk_tail, ws.chunk_flag, ws.cand, ws.candv, ws.tail,
-                     ws.row_flag);
+  const auto kernel = g.M <= 64    ? (shift ? scan_merge_kernel<1, true> : scan_merge_kernel<1, false>)
+                      : g.M <= 128 ? (shift ? scan_merge_kernel<2, true> : scan_merge_kernel<2, false>)
+                                   : (shift ? scan_merge_kernel<4, true> : scan_merge_kernel<4, false>);
+  hipLaunchKernelGGL(kernel, dim3(g.rows), dim3(kScanThreads), 0, s, g, c, inv_tau, ws.chunk_keys, ws.chunk_tail,
+                     ws.chunk_flag, ws.cand, ws.candv, ws.tail, ws.row_flag);
   return hipGetLastError();
 }
 

@@ -129,237 +129,22 @@ __device__ inline void put(T *p, T v) {
     *p = v;
 }
 
-// LDS carve of merge_row for nlists lists of M keys (byte offsets)
-constexpr int kMergeAllPairs = 1024;  // survivors ranked among themselves up to this many
-struct MergeBuf {
-  int top, topv, heads, skeys, scnt, sidx, total;
-};
+// The envelope's bound on a row's segment lists: bytes per list entry and menu
+// slot (the public limit on V and M is stated in these terms; the expansion's LDS
+// layout reserves them).
 __host__ __device__ inline int up16(int b) { return (b + 15) & ~15; }
-__host__ __device__ inline MergeBuf merge_buf(int nlists, int M) {
+__host__ __device__ inline int merge_buf_bytes(int nlists, int M) {
   const int n = nlists * M;
   const int q = (M + nlists - 1) / nlists;
   const int nhp = (nlists * q + 1) & ~1;
-  MergeBuf b;
-  b.top = up16(8 * n);                 // keys: n u64 at 0
-  b.topv = up16(b.top + 8 * M);        // top: M u64
-  b.heads = up16(b.topv + 4 * M);      // topv: M f32
-  b.skeys = up16(b.heads + 8 * nhp);   // heads: nhp u64
-  const int ns_cap = n < kMergeAllPairs ? n : kMergeAllPairs;
-  b.scnt = up16(b.skeys + 8 * (ns_cap + 2));  // skeys: survivors' keys (+ padding)
-  b.sidx = up16(b.scnt + 4 * n);       // scnt: n i32
-  b.total = up16(b.sidx + 2 * n);      // sidx: n i16
-  return b;
-}
-__host__ __device__ inline int merge_buf_bytes(int nlists, int M) { return merge_buf(nlists, M).total; }
-
-// Merge the sorted chunk lists of one row: the row's M best keys and
-// R = log sum over every other element of exp(x / tau).
-//   lists: nlists * M keys (0 = empty slot), each list sorted descending;
-//   tails: per-chunk (max, sum) of the elements not in its list; flags: per chunk.
-// Exact without sorting the lists together:
-//  * thr = the M-th best of the first q = ceil(M / nlists) keys of every list.
-//    Those keys are all in the row, so at least M keys are >= thr and thr is
-//    <= the row's M-th best key: keys below thr go straight to the tail.
-//  * a surviving key's rank below M is the number of larger survivors: a key
-//    outside every list lies below the M keys of its chunk's list, and a list
-//    key above a survivor is a survivor itself.  (With very many survivors the
-//    rank is its position in its own list plus a binary search in every other
-//    list, exact in the same way.)
-// Every key joins the tail through the thread that holds its list position,
-// so the result does not depend on the order the survivors were collected in.
-// buf: merge_buf_bytes(nlists, M) bytes of LDS; red: NT/64 float2.
-// DEV_SCOPE selects device-scope stores (results read by other workgroups).
-// vadd (nullable): candv[m] = logit + vadd[cand[m]] instead of the logit.
-template <int NT, bool DEV_SCOPE, bool SHIFT = false>
-__device__ __attribute__((always_inline)) void merge_row(const uint64_t *lists, int nlists, int M, const float2 *tails,
-                          const int32_t *flags, float c, float inv_tau, uint64_t *buf,
-                          float2 *red, int *flag_lds, int32_t *cand, float *candv, float *tailR,
-                          int32_t *rflag, const float *vadd) {
-  const int tid = threadIdx.x;
-  const int n = nlists * M;
-  const int q = (M + nlists - 1) / nlists;
-  const int nh = nlists * q, nhp = (nh + 1) & ~1;
-  const MergeBuf mb = merge_buf(nlists, M);
-  char *base = reinterpret_cast<char *>(buf);
-  uint64_t *keys = buf;                                           // [n]
-  uint64_t *top = reinterpret_cast<uint64_t *>(base + mb.top);    // [M]
-  float *topv = reinterpret_cast<float *>(base + mb.topv);        // [M]
-  uint64_t *heads = reinterpret_cast<uint64_t *>(base + mb.heads);  // [nhp]
-  uint64_t *skeys = reinterpret_cast<uint64_t *>(base + mb.skeys);  // survivors' keys
-  int32_t *scnt = reinterpret_cast<int32_t *>(base + mb.scnt);    // [n] survivor ranks
-  int16_t *sidx = reinterpret_cast<int16_t *>(base + mb.sidx);    // [n] survivor positions
-  __shared__ uint64_t s_thr;
-  __shared__ int s_ns;
-  if (tid == 0) {
-    *flag_lds = 0;
-    s_ns = 0;
-    s_thr = 1;  // stays 1 (keep every key) when the heads hold fewer than M keys
-    if (nh & 1) heads[nh] = 0ull;
-  }
-  // 0. one round trip: the lists (heads copied on the way), chunk tails and flags
-  Tail t = tail_empty();
-  int bad = 0;
-  {
-    float2 tl = make_float2(0.0f, 0.0f);
-    if (tid < nlists) {
-      tl = tails[tid];
-      bad = flags[tid];
-    }
-    for (int i0 = 0; i0 < n; i0 += 4 * NT) {
-      uint64_t v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + u * NT + tid;
-        v[u] = i < n ? lists[i] : 0ull;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + u * NT + tid;
-        if (i < n) {
-          keys[i] = v[u];
-          const int l = i / M, p = i - l * M;
-          if (p < q) heads[l * q + p] = v[u];
-        }
-      }
-    }
-    if (tid < nlists) t = tail_merge(t, Tail{tl.x, tl.y}, c);
-    for (int i = tid + NT; i < nlists; i += NT) {
-      t = tail_merge(t, Tail{tails[i].x, tails[i].y}, c);
-      bad |= flags[i];
-    }
-  }
-  for (int i = tid; i < M; i += NT) top[i] = 0ull;
-  for (int i = tid; i < nh; i += NT) scnt[i] = 0;
-  __syncthreads();
-  if (bad) atomicOr(flag_lds, bad);
-  // 1. thr: the M-th largest head (q heads per list); each head's count of
-  //    larger heads is split over RS threads
-  {
-    const int np = nhp / 2;
-    const int RS = nh >= NT ? 1 : (NT / nh > 16 ? 16 : NT / nh);
-    const int per = (np + RS - 1) / RS;
-    const ulonglong2 *h2 = reinterpret_cast<const ulonglong2 *>(heads);
-    for (int p = tid; p < nh * RS; p += NT) {
-      const int h = p / RS, j0 = (p - h * RS) * per;
-      const int j1 = j0 + per < np ? j0 + per : np;
-      const uint64_t k = heads[h];
-      int r = 0;
-#pragma unroll 4
-      for (int j = j0; j < j1; ++j) {
-        const ulonglong2 v = h2[j];
-        r += (v.x > k) + (v.y > k);
-      }
-      if (r) atomicAdd(&scnt[h], r);
-    }
-    __syncthreads();
-    for (int h = tid; h < nh; h += NT)
-      if (heads[h] && scnt[h] == M - 1) s_thr = heads[h];
-  }
-  __syncthreads();
-  const uint64_t thr = s_thr;
-  // 2. survivors (keys >= thr) start from their own position; the rest feed the tail
-  for (int i = tid; i < n; i += NT) {
-    const uint64_t k = keys[i];
-    if (!k) continue;
-    if (k >= thr) {
-      const int at = atomicAdd(&s_ns, 1);
-      sidx[at] = (int16_t)i;
-      scnt[at] = i % M;
-      if (at < kMergeAllPairs) skeys[at] = k;
-    } else {
-      tail_add1(t, key_value(k), c);
-    }
-  }
-  __syncthreads();
-  const int ns = s_ns;
-  // 3. rank the survivors; the M best go to top[] and leave keys[] (zeroed)
-  if (ns <= kMergeAllPairs) {
-    // every key above a survivor is itself a survivor or lies below M keys of
-    // its own list, so a survivor's rank among the survivors is its rank in
-    // the row whenever that is below M.  Each count is split over RS threads.
-    if (tid == 0 && (ns & 1)) skeys[ns] = 0ull;  // pad for paired reads
-    for (int sv = tid; sv < ns; sv += NT) scnt[sv] = 0;
-    // the first survivor this thread places: its vadd entry is in flight during the count
-    const float va0 = (vadd && tid < ns) ? vadd[key_index(skeys[tid])] : 0.0f;
-    __syncthreads();
-    const int np = (ns + 1) >> 1;
-    const int RS = ns >= NT ? 1 : (NT / ns > 16 ? 16 : NT / ns);
-    const int per = (np + RS - 1) / RS;
-    const ulonglong2 *s2 = reinterpret_cast<const ulonglong2 *>(skeys);
-    for (int p = tid; p < ns * RS; p += NT) {
-      const int sv = p / RS, j0 = (p - sv * RS) * per;
-      const int j1 = j0 + per < np ? j0 + per : np;
-      const uint64_t k = skeys[sv];
-      int r = 0;
-#pragma unroll 4
-      for (int j = j0; j < j1; ++j) {
-        const ulonglong2 kk = s2[j];
-        r += (kk.x > k) + (kk.y > k);
-      }
-      if (r) atomicAdd(&scnt[sv], r);
-    }
-    __syncthreads();
-    for (int sv = tid; sv < ns; sv += NT) {
-      const int r = scnt[sv];
-      if (r < M) {
-        const uint64_t k = skeys[sv];
-        const float va = sv == tid ? va0 : (vadd ? vadd[key_index(k)] : 0.0f);
-        top[r] = k;
-        topv[r] = key_value(k) + va;
-        keys[sidx[sv]] = 0ull;
-      }
-    }
-  } else {
-    // + the larger keys of every other list: one binary search per (survivor, list)
-    for (int p = tid; p < ns * nlists; p += NT) {
-      const int sv = p / nlists, j = p % nlists;
-      const int i = sidx[sv];
-      if (j == i / M) continue;
-      const uint64_t k = keys[i];
-      const uint64_t *lj = keys + j * M;
-      int lo = 0, hi = M;  // count of lj[] > k (lj is descending)
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (lj[mid] > k)
-          lo = mid + 1;
-        else
-          hi = mid;
-      }
-      if (lo) atomicAdd(&scnt[sv], lo);
-    }
-    __syncthreads();
-    for (int sv = tid; sv < ns; sv += NT) {
-      const int r = scnt[sv];
-      if (r < M) {
-        const uint64_t k = keys[sidx[sv]];
-        top[r] = k;
-        topv[r] = key_value(k) + (vadd ? vadd[key_index(k)] : 0.0f);
-      }
-    }
-    __syncthreads();
-    for (int sv = tid; sv < ns; sv += NT)
-      if (scnt[sv] < M) keys[sidx[sv]] = 0ull;
-  }
-  __syncthreads();
-  // 4. survivors outside the M best join the tail from their list position
-  for (int i = tid; i < n; i += NT) {
-    const uint64_t k = keys[i];
-    if (k >= thr) tail_add1(t, key_value(k), c);  // thr >= 1: empty slots stay out
-  }
-  t = block_tail<NT>(t, c, red);
-  const float s0 = SHIFT && top[0] ? row_shift(key_value(top[0])) : 0.0f;
-  for (int i = tid; i < M; i += NT) {
-    const uint64_t k = top[i];
-    put<DEV_SCOPE>(cand + i, k ? (int32_t)key_index(k) : (int32_t)-1);
-    float v = k ? topv[i] : -__builtin_huge_valf();
-    if (SHIFT && k) v = (key_value(k) - s0) + (vadd ? vadd[key_index(k)] : 0.0f);
-    put<DEV_SCOPE>(candv + i, v);
-  }
-  if (tid == 0) {
-    put<DEV_SCOPE>(tailR, t.s > 0.0f ? (t.m - s0) * inv_tau + logf(t.s) : -__builtin_huge_valf());
-    put<DEV_SCOPE>(rflag, (int32_t)(*flag_lds ? DT_TREE_NONFINITE : 0));
-  }
-  __syncthreads();
+  const int ns_cap = n < 1024 ? n : 1024;
+  int b = up16(8 * n);
+  b = up16(b + 8 * M);
+  b = up16(b + 4 * M);
+  b = up16(b + 8 * nhp);
+  b = up16(b + 8 * (ns_cap + 2));
+  b = up16(b + 4 * n);
+  return up16(b + 2 * n);
 }
 
 // ---------------------------------------------------------------------------
@@ -432,6 +217,52 @@ __device__ inline uint64_t merge_halves(uint64_t a, uint64_t b, bool desc, Tail 
   return bitonic_clean64(hi, desc);
 }
 
+// a wave's list: entry r * 64 + lane, descending (0: empty)
+template <int R>
+struct WaveList {
+  uint64_t k[R];
+};
+
+// 64 ascending keys into the list; the 64 that drop out join the lanes' tails
+template <int R>
+__device__ inline void list_insert(WaveList<R> &l, uint64_t asc, Tail &tail, float c) {
+#pragma unroll
+  for (int r = 0; r < R - 1; ++r) {
+    const bool ga = l.k[r] > asc;
+    const uint64_t hi = ga ? l.k[r] : asc, lo = ga ? asc : l.k[r];
+    l.k[r] = bitonic_clean64(hi, true);
+    asc = bitonic_clean64(lo, false);
+  }
+  l.k[R - 1] = merge_halves(l.k[R - 1], asc, true, tail, c);
+}
+
+// another list (other(i): its entry i, descending) into this wave's: the best 64 R
+// stay, the rest join the lanes' tails
+template <int R, typename F>
+__device__ inline void list_merge(WaveList<R> &l, F other, Tail &tail, float c) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint64_t o = other(R * 64 - 1 - (r * 64 + lane));
+    const bool ga = l.k[r] > o;
+    const uint64_t lo = ga ? o : l.k[r];
+    l.k[r] = ga ? l.k[r] : o;
+    tail_add1(tail, lo ? key_value(lo) : -__builtin_huge_valf(), c);
+  }
+  // (now bitonic over the 64 R entries)
+#pragma unroll
+  for (int h = R / 2; h > 0; h >>= 1)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((r & h) == 0) {
+        const uint64_t x = l.k[r], y = l.k[r + h];
+        l.k[r] = x > y ? x : y;
+        l.k[r + h] = x > y ? y : x;
+      }
+#pragma unroll
+  for (int r = 0; r < R; ++r) l.k[r] = bitonic_clean64(l.k[r], true);
+}
+
 // full bitonic sort of 64 keys (one per lane), descending or ascending
 __device__ inline uint64_t wave_sort64(uint64_t v, bool desc) {
   const int lane = threadIdx.x & 63;
@@ -461,8 +292,8 @@ __host__ __device__ inline bool wave_merge_fits(int nlists, int M) {
   return M <= 64 && nlists <= kWaveMergeLists;
 }
 
-// The same results as merge_row (the row's M best keys, R over the rest, the
-// row flag), computed by the calling wave alone; wave_merge_fits must hold.
+// The row's M best keys, R = log sum over every other element of exp(x / tau) and
+// the row flag, computed by the calling wave alone; wave_merge_fits must hold.
 template <bool DEV_SCOPE, bool SHIFT = false>
 __device__ __attribute__((always_inline)) void merge_row_wave(
     const uint64_t *lists, int nlists, int M, const float2 *tails, const int32_t *flags, float c,
@@ -587,6 +418,91 @@ __device__ __attribute__((always_inline)) void merge_row_tree(
       put<DEV_SCOPE>(rflag, (int32_t)(any_bad ? DT_TREE_NONFINITE : 0));
     }
   }
+}
+
+// The same results for any number of lists and M <= 64 R: the lists are dealt to
+// the waves, each merges its own in registers (the next one's loads in flight),
+// and the waves' lists meet in LDS (xbuf: NT R keys).  Bound by the merges'
+// chains of lane exchanges.  Against ranking the survivors of a threshold in LDS:
+// 8 lists of 128 keys, 128 rows, 19.6 -> 4.2 us; 4 lists of 64, 512 rows, 6.5 -> 4.8.
+// DEV_SCOPE selects device-scope stores (results read by other workgroups).
+// vadd (nullable): candv[m] = logit + vadd[cand[m]] instead of the logit.
+template <bool DEV_SCOPE, int NT, int R, bool SHIFT = false>
+__device__ __attribute__((always_inline)) void merge_row_lists(
+    const uint64_t *lists, int nlists, int M, const float2 *tails, const int32_t *flags, float c,
+    float inv_tau, uint64_t *xbuf, float2 *red, int *flag_lds, int32_t *cand, float *candv, float *tailR,
+    int32_t *rflag, const float *vadd) {
+  constexpr int W = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid == 0) *flag_lds = 0;
+  WaveList<R> l;
+  uint64_t nx[R];  // the next list, reversed
+  auto next = [&](int j) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = R * 64 - 1 - (r * 64 + lane);
+      nx[r] = (j < nlists && i < M) ? lists[(size_t)j * M + i] : 0ull;
+    }
+  };
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = r * 64 + lane;
+    l.k[r] = (wave < nlists && i < M) ? lists[(size_t)wave * M + i] : 0ull;
+  }
+  next(wave + W);
+  Tail t = tail_empty();
+  int bad = 0;
+  for (int i = tid; i < nlists; i += NT) {
+    const float2 tl = tails[i];
+    t = tail_merge(t, Tail{tl.x, tl.y}, c);
+    bad |= flags[i];
+  }
+  __syncthreads();
+  if (bad) atomicOr(flag_lds, bad);
+  for (int j = wave + W; j < nlists; j += W) {
+    uint64_t cur[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) cur[r] = nx[r];
+    next(j + W);
+    // (entry 64 R - 1 - (64 r + lane) is the one loaded as cur[r])
+    list_merge<R>(l, [&](int i) { return cur[(R * 64 - 1 - i) >> 6]; }, t, c);
+  }
+#pragma unroll
+  for (int s = 1; s < W; s <<= 1) {
+    if (s < nlists) {  // (uniform)
+      if ((wave & (2 * s - 1)) == s)
+#pragma unroll
+        for (int r = 0; r < R; ++r) xbuf[wave * 64 * R + r * 64 + lane] = l.k[r];
+      __syncthreads();
+      if ((wave & (2 * s - 1)) == 0 && wave + s < nlists)
+        list_merge<R>(l, [&](int i) { return xbuf[(wave + s) * 64 * R + i]; }, t, c);
+    }
+  }
+  float va[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool mine = wave == 0 && l.k[r] != 0ull;
+    if (mine && r * 64 + lane >= M) tail_add1(t, key_value(l.k[r]), c);
+    va[r] = (mine && r * 64 + lane < M && vadd) ? vadd[key_index(l.k[r])] : 0.0f;
+  }
+  t = block_tail<NT>(t, c, red);
+  if (wave == 0) {
+    const float s0 = SHIFT ? row_shift(readlane_f(l.k[0] ? key_value(l.k[0]) : 0.0f, 0)) : 0.0f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = r * 64 + lane;
+      if (i < M) {
+        const uint64_t k = l.k[r];
+        put<DEV_SCOPE>(cand + i, k ? (int32_t)key_index(k) : (int32_t)-1);
+        put<DEV_SCOPE>(candv + i, k ? (key_value(k) - s0) + va[r] : -__builtin_huge_valf());
+      }
+    }
+    if (lane == 0) {
+      put<DEV_SCOPE>(tailR, t.s > 0.0f ? (t.m - s0) * inv_tau + logf(t.s) : -__builtin_huge_valf());
+      put<DEV_SCOPE>(rflag, (int32_t)(*flag_lds ? DT_TREE_NONFINITE : 0));
+    }
+  }
+  __syncthreads();
 }
 
 }  // namespace sel

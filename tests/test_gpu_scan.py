@@ -236,3 +236,16 @@ def test_scan_rows_at_any_offset(dtype, per, M):
             # fp32 sums of V terms over 256 threads and a tree: (V / 256 + 16) roundings of 2^-24,
             # each term exact to a few ulps of its exponent
             assert tail[r] == rR or abs(tail[r] - rR) <= (V / 256 + 64) * 2.0 ** -24 * max(1.0, abs(rR)), (off, V, r)
+
+
+@pytest.mark.parametrize("M", [1, 63, 64, 65, 128, 129, 256])
+@pytest.mark.parametrize("nlists", [2, 3, 4, 5, 9, 21])
+def test_scan_merge_of_many_segments(nlists, M):
+    # two rows are cut into one segment per 10240 elements: fewer lists than waves,
+    # as many, and several per wave, the last list shorter than M; runs of ties cross
+    # the segments, one row's best values all lie in one segment
+    V = (nlists - 1) * 10240 + max(1, M // 2)
+    x = synth.peaked_logits(12, 0, 2, V, synth.DT_F32, 1, 4, 6.0, 12.0).reshape(2, V)
+    x[0, ::641] = 14.0
+    x[1, 10200:10200 + min(300, V - 10200)] += 30.0
+    _check(x, synth.DT_F32, M, 1.0, case=f"{nlists} lists M={M}")
