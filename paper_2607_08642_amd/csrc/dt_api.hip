@@ -293,7 +293,7 @@ static dt_status plan_init(dt_plan *p, int V, int d_e, int d_h, int wdt, int mod
   p->max_lds = (size_t)maxlds;
   p->frontier_w = o.frontier_width;
   p->spin_limit = o.debug_spin_limit;
-  p->grow_occ = M <= 64 && B <= 64 ? dt::grow_max_occ(wdt, d_h, L, B, ncu, nxcd) : 0;
+  p->grow_occ = M <= 64 && B <= 64 ? dt::grow_max_occ(o.scorer, wdt, d_h, L, B, ncu, nxcd) : 0;
   p->device = dev;
   return DT_OK;
 }
@@ -500,7 +500,9 @@ static dt_status build_tree_on(dt_plan *plan, const void *logits, int batch, con
                                         prof ? ev[0] : nullptr, prof ? ev[1] : nullptr);
   if (e != hipSuccess) return hip_fail(e, "scan launch");
   dt::ExpMode mode;
-  if (plan->scorer == DT_SCORER_MARG) {
+  if (ws.grow) {
+    // (that kernel's instances take the scorers themselves)
+  } else if (plan->scorer == DT_SCORER_MARG) {
     mode.nocorr = 1;
   } else if (plan->scorer == DT_SCORER_STATIC) {
     // the greedy chain (k = 1, L pops) writes every depth's corrected menu;

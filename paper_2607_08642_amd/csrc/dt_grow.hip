@@ -58,6 +58,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int GT = kGrowThreads;
 constexpr int GW = GT / 64;
@@ -65,11 +66,15 @@ constexpr int CH = kChunkNodes;
 constexpr int UW = kGrowUnits;
 constexpr int MP = 64;                // slots of a menu, padded
 constexpr int kTile = 272;            // floats of a 16 x 16 gate tile in LDS (16-row groups of 4, padded)
+constexpr int kChainTile = 48;        // ... of its first three columns
 constexpr int kGh = 4 * UW;           // floats kept of an expanded node: W_hh S (r, z, n), S
 constexpr int SNS = UW + 4;           // row stride of the new states in LDS
 constexpr uint32_t kEmptyWord = 0xFFFFFFFFu;  // a partial correction that has not arrived
 constexpr int kGrowSpin = 1 << 18;    // default bound of a wait
 static_assert(GW == 4 && CH == 16 && UW == 32, "the work split below");
+// the children function of an instance: conditional, the depths' marginals, or the
+// menus of a greedy chain
+enum { kCond = DT_SCORER_COND, kMarg = DT_SCORER_MARG, kStatic = DT_SCORER_STATIC };
 
 struct GrowArgs {
   int L, M, B, k, G, norm_mode, pos_offset, batch, nchunks, nxcd, ngroups, spin_limit;
@@ -96,7 +101,7 @@ struct GrowArgs {
 struct GrowLds {
   int list, top, gpart, sn, anc, red, ints, gh, ids, vals, tails, total;
 };
-__host__ __device__ inline GrowLds grow_layout(int L, int B) {
+__host__ __device__ inline GrowLds grow_layout(int L, int B, int arm) {
   GrowLds l;
   int o = 0;
   auto take = [&](int bytes) {
@@ -106,19 +111,20 @@ __host__ __device__ inline GrowLds grow_layout(int L, int B) {
   };
   l.list = take((CH + 1) * MP * 8);  // a step's children, and the old entries beside them
   l.top = take(64 * 8);
-  l.gpart = take(GW * 6 * kTile * 4);
-  l.sn = take(CH * SNS * 4);
+  l.gpart = take(arm == kCond ? GW * 6 * kTile * 4 : arm == kStatic ? GW * 6 * kChainTile * 4 : 0);
+  l.sn = take(arm == kCond ? CH * SNS * 4 : arm == kStatic ? GW * UW * 4 : 0);
   l.anc = take(64 * 8);
   l.red = take(GW * 8);
   l.ints = take(16 * 4);
-  l.gh = take(2 * B * kGh * 4);
-  l.ids = take(L * MP * 4);
-  l.vals = take(L * MP * 4);
+  l.gh = take(arm == kCond ? 2 * B * kGh * 4 : 0);
+  const int sets = arm == kStatic ? 2 : 1;  // (the tree a member builds, and the chain under way)
+  l.ids = take(sets * L * MP * 4);
+  l.vals = take(sets * L * MP * 4);
   l.tails = take(L * 4);
   l.total = o;
   return l;
 }
-enum { I_STATUS, I_CNT0, I_CNT1, I_SLOT };
+enum { I_STATUS, I_CNT0, I_CNT1, I_SLOT, I_LATE0, I_LATE1 };
 
 // ---- device-scope access, barriers ------------------------------------------
 constexpr int kSc1 = 16;  // cache-policy bit: device scope
@@ -244,12 +250,30 @@ struct State<uint16_t> {
     st2(r, o + 2 * dh, __builtin_bit_cast(uint16_t, m));
     st2(r, o + 4 * dh, __builtin_bit_cast(uint16_t, l));
   }
+  // ... with no half word that reads as empty
+  static __device__ inline void send(__amdgpu_buffer_rsrc_t r, int row, int dh, int j, float x) {
+    const __bf16 h = (__bf16)x;
+    const float r1 = x - (float)h;
+    const __bf16 m = (__bf16)r1;
+    const __bf16 l = (__bf16)(r1 - (float)m);
+    const int o = row + j * 2;
+    auto full = [](__bf16 v) {
+      const uint16_t b = __builtin_bit_cast(uint16_t, v);
+      return b == 0xFFFFu ? (uint16_t)0x7FC0u : b;
+    };
+    st2(r, o, full(h));
+    st2(r, o + 2 * dh, full(m));
+    st2(r, o + 4 * dh, full(l));
+  }
 };
 template <>
 struct State<float> {
   static __host__ __device__ constexpr int row_bytes(int dh) { return 4 * dh; }
   static __device__ inline void store(__amdgpu_buffer_rsrc_t r, int row, int, int j, float x) {
     st4(r, row + j * 4, as_u(x));
+  }
+  static __device__ inline void send(__amdgpu_buffer_rsrc_t r, int row, int, int j, float x) {
+    st4(r, row + j * 4, as_u(x) == kEmptyWord ? 0x7FC00000u : as_u(x));
   }
 };
 
@@ -295,6 +319,23 @@ struct Gates<uint16_t, KPW, FULL, OCC> {
       const int off = one ? (in1 ? i * 64 : kOut) : (in3 ? (i / 3) * 64 + (i % 3) * 2 * dh : kOut);
       f.s[i] = ld16(st, o + off);
     }
+  }
+  // a chain's node (off: the lane's plane of its row, or out of range), and whether
+  // part of it has not arrived
+  static __device__ inline void fetch_one(__amdgpu_buffer_rsrc_t st, int off, int k0, int k1, int lane, Frag &f) {
+    const int o = off + (k0 * 32 + (lane >> 4) * 8) * 2;
+#pragma unroll
+    for (int i = 0; i < KPW; ++i) f.s[i] = ld16(st, FULL || k0 + i < k1 ? o + i * 64 : kOut);
+  }
+  static __device__ inline bool empty(const Frag &f) {
+    u16x2 m = {0, 0};
+#pragma unroll
+    for (int i = 0; i < KPW; ++i) {
+      const uint32_t w[4] = {f.s[i].x, f.s[i].y, f.s[i].z, f.s[i].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[e]));
+    }
+    return m.x == 0xFFFFu || m.y == 0xFFFFu;
   }
   template <bool ONE>
   __device__ inline void mul(__amdgpu_buffer_rsrc_t st, int rowoff, int dh, int k0, int k1, int lane, Frag &f,
@@ -345,6 +386,16 @@ struct Gates<float, KPW, FULL, OCC> {
     for (int i = 0; i < 2 * KPW; ++i)
       f.s[i] = __builtin_bit_cast(float4, ld16(st, o + (FULL || 2 * k0 + i < 2 * k1 ? i * 64 : kOut)));
   }
+  static __device__ inline void fetch_one(__amdgpu_buffer_rsrc_t st, int off, int k0, int k1, int lane, Frag &f) {
+    fetch(st, true, off, 0, k0, k1, lane, f);
+  }
+  static __device__ inline bool empty(const Frag &f) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < 2 * KPW; ++i)
+      m = max(max(m, as_u(f.s[i].x)), max(as_u(f.s[i].y), max(as_u(f.s[i].z), as_u(f.s[i].w))));
+    return m == kEmptyWord;
+  }
   template <bool ONE>
   __device__ inline void mul(__amdgpu_buffer_rsrc_t, int, int, int, int, int, Frag &f, f32x4 (&acc)[6]) const {
 #pragma unroll
@@ -363,11 +414,14 @@ struct Gates<float, KPW, FULL, OCC> {
 };
 
 // KPW: k steps of 32 hidden units per wave at most (d_h <= 128 KPW); SG > 0 fixes
-// the members (and with them d_h) at compile time; OCC: workgroups a CU is to hold
-template <typename TW, int KPW, int SG, int OCC>
+// the members (and with them d_h) at compile time; OCC: workgroups a CU is to hold;
+// ARM: the children function.  A marginal tree needs no state: one workgroup.
+// Menus of a greedy chain: the group's members run the chains of up to G trees,
+// then each builds one of those trees from its menus.
+template <typename TW, int KPW, int SG, int OCC, int ARM>
 __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const GrowLds ly = grow_layout(a.L, a.B);
+  const GrowLds ly = grow_layout(a.L, a.B, ARM);
   uint64_t *list = reinterpret_cast<uint64_t *>(smem + ly.list);
   uint64_t *top = reinterpret_cast<uint64_t *>(smem + ly.top);
   float *gpart = reinterpret_cast<float *>(smem + ly.gpart);
@@ -407,24 +461,51 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
 
   // ---- prologue: weights, empty exchange buffers, this member's rows of the scan
   const int k0 = nks * wave / GW, k1 = nks * (wave + 1) / GW;  // this wave's k steps of W_hh S
-  Gates<TW, KPW, FULL, OCC> gates;
-  gates.load(a.whh, member * 2, nks, k0, k1);
-  const float bhn = a.b_hh[2 * dh + member * UW + (lane & 31)];
+  using Gt = Gates<TW, KPW, FULL, OCC>;
+  Gt gates;
+  if constexpr (ARM != kMarg) gates.load(a.whh, member * 2, nks, k0, k1);
+  const float bhn = ARM != kMarg ? a.b_hh[2 * dh + member * UW + (lane & 31)] : 0.0f;
   float *const gp = a.part + (size_t)group * 3 * CH * G * MP;
   const __amdgpu_buffer_rsrc_t rpart = rsrc(gp);
   const __amdgpu_buffer_rsrc_t rstate = rsrc(a.states + (size_t)group * 2 * CH * State<TW>::row_bytes(dh));
   const uint4 empty4 = make_uint4(kEmptyWord, kEmptyWord, kEmptyWord, kEmptyWord);
   // byte offset of (buffer, column, member): this thread's 16 bytes of column tid / 16
   auto part_off = [&](int buf, int c, int j) { return ((buf * CH + c) * G + j) * (MP * 4); };
+  // chains: one column in four buffers, the states beside them
+  constexpr int kPieces = (Gt::kPlanes ? 6 : 4) * UW / 16;  // 16-byte pieces of a member's state
+  auto chain_off = [&](int buf, int j) { return (buf * G + j) * (MP * 4); };
+  auto chain_piece = [&](int buf, int i) {
+    return buf * State<TW>::row_bytes(dh) + (Gt::kPlanes ? (i >> 2) * 2 * dh + member * (2 * UW) + (i & 3) * 16
+                                                         : member * (4 * UW) + i * 16);
+  };
+  if constexpr (ARM == kCond) {
 #pragma unroll
-  for (int b = 0; b < 3; ++b) st16(rpart, part_off(b, tid >> 4, member) + (tid & 15) * 16, empty4);
+    for (int b = 0; b < 3; ++b) st16(rpart, part_off(b, tid >> 4, member) + (tid & 15) * 16, empty4);
+  } else if constexpr (ARM == kStatic) {
+    if (tid < 64) st16(rpart, chain_off(tid >> 4, member) + (tid & 15) * 16, empty4);
+    if (tid < 4 * kPieces) st16(rstate, chain_piece(tid / kPieces, tid % kPieces), empty4);
+  }
   if (tid == 0) {
     ints[I_STATUS] = 0;
     ints[I_CNT0] = 0;
     ints[I_CNT1] = 0;
+    ints[I_LATE0] = 0;
+    ints[I_LATE1] = 0;
   }
-  int cell = member;  // rows of the group's trees, dealt to its members
+  // rows of the group's trees, dealt to its members (a lone workgroup's to its waves)
+  int cell = ARM == kMarg ? wave : member;
   for (int t = group; t < a.batch && !a.compact; t += a.ngroups) {
+    if constexpr (ARM == kMarg) {
+      for (; cell < L; cell += GW) {
+        const int row = t * L + cell;
+        sel::merge_row_wave<true, true>(a.ckeys + (size_t)row * a.nchunks * M, a.nchunks, M,
+                                        a.ctail + (size_t)row * a.nchunks, a.cflag + (size_t)row * a.nchunks, a.c2,
+                                        a.inv_tau, a.cand + (size_t)row * M, a.candv + (size_t)row * M,
+                                        a.tailR + row, a.rflag + row, nullptr);
+      }
+      cell -= L;
+      continue;
+    }
     for (; cell < L; cell += G) {
       const int row = t * L + cell;
       sel::merge_row_tree<true, GT, true>(a.ckeys + (size_t)row * a.nchunks * M, a.nchunks, M,
@@ -458,15 +539,8 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
   int par = 0;              // which list counter the next step uses
   int xpar = 0;             // which half of the states the next exchange uses
 
-  for (int t = group; t < a.batch; t += a.ngroups) {
-    dt_tree o = a.out;
-    int32_t *otok = o.tokens + (size_t)t * B;
-    int32_t *opar = o.parents + (size_t)t * B;
-    int32_t *odep = o.depth + (size_t)t * B;
-    int32_t *opos = o.position_ids + (size_t)t * B;
-    float *osc = o.scores + (size_t)t * B;
-    uint8_t *omask = o.mask + (size_t)t * B * B;
-    // ---- the tree's merged rows: ids, values, tails, flags -----------------------
+  // a tree's merged rows: ids, values, tails, flags
+  auto load_rows = [&](int t, int32_t *ids, float *vals) {
     lds_barrier();  // (the previous tree's rows are read out)
     if (tid == 0) ints[I_STATUS] = dead ? DT_TREE_TIMEOUT : 0;
     if (!dead) {
@@ -477,14 +551,14 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
       const int m = lane < M ? lane : M - 1;
       for (int d0 = wave; d0 < L; d0 += 4 * GW) {
         uint32_t id[4], v[4];
-#pragma unroll
+  #pragma unroll
         for (int i = 0; i < 4; ++i) {  // (rows past the last: it again)
           const int d = d0 + i * GW < L ? d0 + i * GW : L - 1;
           id[i] = ld4(rid, (d * M + m) * 4);
           v[i] = ld4(rv, (d * M + m) * 4);
         }
         asm volatile("" : "+v"(id[0]), "+v"(id[1]), "+v"(id[2]), "+v"(id[3]));  // (all in flight together)
-#pragma unroll
+  #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int d = d0 + i * GW < L ? d0 + i * GW : L - 1;
           // (dead slots, -1: row 0, unused)
@@ -493,11 +567,197 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
         }
       }
       if (tid < L) tails[tid] = tl;
-      if (tid < kGh) gh[tid] = 0.0f;  // (a zero root state; h0's is written by the root step)
+      if (ARM == kCond && tid < kGh) gh[tid] = 0.0f;  // (a zero root state; h0's is written by the root step)
       lds_barrier();
       if (fl) atomicOr(&ints[I_STATUS], fl);
     }
     lds_barrier();
+  };
+  // the depths' menus, normalised where they lie (values to be scaled first)
+  auto normalise = [&](float scale) {
+    for (int d = wave; d < L; d += GW) {
+      const float x = vals[d * MP + lane], R = tails[d];
+      const float z = x > NEG_INF ? x * scale : NEG_INF;
+      const bool tail = a.norm_mode == DT_NORM_TAIL && R > NEG_INF;
+      float mx = wave_all(z, [](float p, float q) { return fmaxf(p, q); });
+      if (tail) mx = fmaxf(mx, R);
+      float sum = wave_all(z > NEG_INF ? exp_hw(z - mx) : 0.0f, [](float p, float q) { return p + q; });
+      if (tail) sum += exp_hw(R - mx);
+      vals[d * MP + lane] = z > NEG_INF ? z - (mx + log_hw(sum)) : NEG_INF;
+    }
+    lds_barrier();
+  };
+
+  // The greedy chain of a tree (Cond-static): vals becomes each depth's corrected
+  // and scaled values.  One node per step, so every wave keeps the state itself
+  // and a step is a GRU, a 32-term dot product per slot, one exchange and W_hh S,
+  // with one barrier (the waves' parts of W_hh S).  States and corrections are
+  // sent together and both polled for, so no store is waited for: four buffers
+  // rotate, and the one that step s + 2 uses is emptied at step s by the waves
+  // that fill it -- a reader of step s + 2 has seen that wave's words of step
+  // s + 1, sent after the wave had waited for loads issued behind the emptying
+  // stores; and a wave that empties has seen words of step s - 1 of every wave,
+  // sent after the barrier behind their reads of step s - 2, the buffer's last.
+  // P and U rows of the next depth's menu are loaded a step ahead (P into L2).
+  uint32_t xs = 0;
+  auto chain = [&](int t, const int32_t *ids, float *vals) {
+    const int u = lane & 31, slot = 4 * (lane & 15) + (lane >> 4), cs = wave * 16 + (lane >> 2);
+    const int col = lane & 15;
+    float S = a.h0 ? a.h0[(size_t)t * dh + member * UW + u] : 0.0f;
+    float gr = 0.0f, gz = 0.0f, gn = 0.0f, xr = 0.0f, xz = 0.0f, xn = 0.0f, pf;
+    float4 u0, u1;
+    auto ahead = [&](int d) {
+      const float *ur = a.U_all + (size_t)ids[d * MP + cs] * dh + member * UW + (lane & 3) * 8;
+      u0 = *reinterpret_cast<const float4 *>(ur);
+      u1 = *reinterpret_cast<const float4 *>(ur + 4);
+      const int i = tid < 3 * MP ? tid : 0;
+      pf = a.P_all[(size_t)ids[d * MP + i / 3] * (3 * dh) + (i % 3) * dh + member * UW];
+    };
+    ahead(0);
+    for (int d = 0; d < L; ++d) {
+      const float x = vals[d * MP + slot];
+      const int my_id = ids[d * MP + slot];
+      const bool corr = d > 0 || a.h0 != nullptr, grows = corr && d + 1 < L;
+      typename Gt::Frag frag;
+      float dl = x;
+      if (corr) {
+        if (d > 0) {
+          const float r = sigmoid_fast(xr + gr);
+          const float z = sigmoid_fast(xz + gz);
+          const float nn = tanh_fast(xn + r * (gn + bhn));
+          S = (1.0f - z) * nn + z * S;
+        }
+        if (lane < UW) Sn[wave * UW + u] = S;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        const float4 *sp = reinterpret_cast<const float4 *>(Sn + wave * UW + (lane & 3) * 8);
+        const float4 s0 = sp[0], s1 = sp[1];
+        float dot = ((u0.x * s0.x + u0.y * s0.y) + (u0.z * s0.z + u0.w * s0.w)) +
+                    ((u1.x * s1.x + u1.y * s1.y) + (u1.z * s1.z + u1.w * s1.w));
+        dot += sel::dpp_f<0xB1>(dot);
+        dot += sel::dpp_f<0x4E>(dot);
+        const int b = xs & 3, eb = b ^ 2;
+        ++xs;
+        if ((lane & 3) == 0) st4(rpart, chain_off(b, member) + cs * 4, as_u(dot) == kEmptyWord ? 0x7FC00000u : as_u(dot));
+        if (wave == 0 && lane < UW) State<TW>::send(rstate, b * State<TW>::row_bytes(dh), dh, member * UW + u, S);
+        if ((lane & 3) == 0) st4(rpart, chain_off(eb, member) + cs * 4, kEmptyWord);
+        if (wave == 0 && lane < kPieces) st16(rstate, chain_piece(eb, lane), empty4);
+        float4 s;
+        int spins = 0;
+        const int fo = grows && col < (Gt::kPlanes ? 3 : 1) ? b * State<TW>::row_bytes(dh) + (Gt::kPlanes ? col * 2 * dh : 0)
+                                                            : kOut;
+        for (;;) {
+          uint4 v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int j = 4 * i + (lane >> 4);
+            v[i] = ld16(rpart, SG == 16 || j < G ? chain_off(b, j) + (lane & 15) * 16 : kOut);
+          }
+          gates.fetch_one(rstate, fo, k0, k1, lane, frag);
+          bool late = Gt::empty(frag);
+          uint32_t mx = 0;
+          s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            mx = max(max(mx, v[i].x), max(v[i].y, max(v[i].z, v[i].w)));
+            s.x += as_f(v[i].x);
+            s.y += as_f(v[i].y);
+            s.z += as_f(v[i].z);
+            s.w += as_f(v[i].w);
+          }
+          late |= mx == kEmptyWord;
+          if (__ballot(late) == 0) break;
+          if (++spins > a.spin_limit) {
+            if (lane == 0) ints[I_LATE0 + (d & 1)] = 1;
+            break;
+          }
+          asm volatile("" ::: "memory");  // (load again)
+        }
+        dl = x + fold16(fold32(s.x, s.z), fold32(s.y, s.w));
+      }
+      // the next node: the best slot, ties to the lower
+      const float z = x > NEG_INF ? dl * a.inv_tau : NEG_INF;
+      const float mx = wave_all(z, [](float p, float q) { return fmaxf(p, q); });
+      uint64_t best = __ballot(z == mx);
+      if (best & (best - 1)) {
+        const float ms = wave_all(z == mx ? (float)slot : 64.0f, [](float p, float q) { return fminf(p, q); });
+        best = __ballot(z == mx && (float)slot == ms);
+      }
+      const int id = __builtin_amdgcn_readlane(my_id, best ? __builtin_ctzll(best) : 0);
+      const float *pr = a.P_all + (size_t)id * (3 * dh) + member * UW + u;
+      xr = pr[0];
+      xz = pr[dh];
+      xn = pr[2 * dh];
+      ahead(d + 1 < L ? d + 1 : d);
+      if (grows) {
+        f32x4 acc[6];
+        gates.template mul<true>(rstate, 0, dh, k0, k1, lane, frag, acc);
+        if (col < 3) {
+#pragma unroll
+          for (int g = 0; g < 6; ++g)
+            *reinterpret_cast<f32x4 *>(gpart + (wave * 6 + g) * kChainTile + col * 16 + (lane >> 4) * 4) = acc[g];
+        }
+      }
+      lds_barrier();
+      if (wave == 0) vals[d * MP + slot] = z;
+      if (ints[I_LATE0 + (d & 1)]) {  // (a wave a step ahead writes the other word)
+        dead = true;
+        break;
+      }
+      if (!(mx > NEG_INF)) break;  // (no child: nothing deeper is reached)
+      if (grows) {
+        // this half's waves' parts, the planes, then the other half's
+        const float *p = gpart + ((lane >> 5) * 12 + (u >> 4) * 3) * kChainTile + (u & 15);
+        float w3[3];
+#pragma unroll
+        for (int g = 0; g < 3; ++g) {
+          float c3[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) c3[q] = p[g * kChainTile + q * 16] + p[(6 + g) * kChainTile + q * 16];
+          w3[g] = (c3[2] + c3[1]) + c3[0];
+        }
+        gr = fold32(w3[0], w3[0]);
+        gz = fold32(w3[1], w3[1]);
+        gn = fold32(w3[2], w3[2]);
+      }
+    }
+    asm volatile("" ::"v"(pf));
+    lds_barrier();
+  };
+  constexpr bool ST = ARM == kStatic;
+  for (int t0 = group; t0 < a.batch; t0 += ST ? a.ngroups * G : a.ngroups) {
+    int t = t0;
+    if constexpr (ST) {
+      int own = 0;
+      for (int j = 0; j < G && t0 + j * a.ngroups < a.batch; ++j) {
+        const int tc = t0 + j * a.ngroups;
+        int32_t *cids = j == member ? ids : ids + L * MP;
+        float *cvals = j == member ? vals : vals + L * MP;
+        load_rows(tc, cids, cvals);
+        int st = ints[I_STATUS];
+        if (!(st & (DT_TREE_NONFINITE | DT_TREE_TIMEOUT))) {
+          chain(tc, cids, cvals);
+          if (dead) st |= DT_TREE_TIMEOUT;
+        }
+        if (j == member) own = st;
+      }
+      t = t0 + member * a.ngroups;
+      if (t >= a.batch) return;  // (no tree of this round, nor of a later one)
+      lds_barrier();
+      if (tid < L) tails[tid] = as_f(ld4(rsrc(a.tailR + (size_t)t * L), tid * 4));
+      if (tid == 0) ints[I_STATUS] = own;
+      lds_barrier();
+      normalise(1.0f);
+    } else {
+      load_rows(t, ids, vals);
+      if constexpr (ARM == kMarg) normalise(a.inv_tau);
+    }
+    dt_tree o = a.out;
+    int32_t *otok = o.tokens + (size_t)t * B;
+    int32_t *opar = o.parents + (size_t)t * B;
+    int32_t *odep = o.depth + (size_t)t * B;
+    int32_t *opos = o.position_ids + (size_t)t * B;
+    float *osc = o.scores + (size_t)t * B;
+    uint8_t *omask = o.mask + (size_t)t * B * B;
     const bool empty_tree = ints[I_STATUS] & (DT_TREE_NONFINITE | DT_TREE_TIMEOUT);
 
     // ---- the candidate list: lane i holds entry i -----------------------------
@@ -525,7 +785,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
       asm volatile("" : "+v"(lane_));
       const int lane = lane_, tid = wave * 64 + lane;
       const int slot = 4 * (lane & 15) + (lane >> 4);  // this lane's slot of a menu
-      const bool corr = d > 0 || a.h0 != nullptr;  // (a zero root state corrects nothing)
+      const bool corr = ARM == kCond && (d > 0 || a.h0 != nullptr);  // (a zero root state corrects nothing)
       float4 uf[UW / 16];  // U rows of the menu (rows 16 wave ..), this member's units
       if (corr) {
         const int m = wave * 16 + (lane & 15);
@@ -706,12 +966,15 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           if (h == 1 && !two) break;
-          const float z = x > NEG_INF ? dl[h] * a.inv_tau : NEG_INF;  // slots >= M hold -inf
-          float mx = wave_all(z, [](float p, float q) { return fmaxf(p, q); });
-          if (tail) mx = fmaxf(mx, R);
-          float sum = wave_all(z > NEG_INF ? exp_hw(z - mx) : 0.0f, [](float p, float q) { return p + q; });
-          if (tail) sum += exp_hw(R - mx);
-          const float lv = z > NEG_INF ? z - (mx + log_hw(sum)) : NEG_INF;
+          float lv = x;  // (menus already normalised)
+          if constexpr (ARM == kCond) {
+            const float z = x > NEG_INF ? dl[h] * a.inv_tau : NEG_INF;  // slots >= M hold -inf
+            float mx = wave_all(z, [](float p, float q) { return fmaxf(p, q); });
+            if (tail) mx = fmaxf(mx, R);
+            float sum = wave_all(z > NEG_INF ? exp_hw(z - mx) : 0.0f, [](float p, float q) { return p + q; });
+            if (tail) sum += exp_hw(R - mx);
+            lv = z > NEG_INF ? z - (mx + log_hw(sum)) : NEG_INF;
+          }
           const uint32_t ghi = __builtin_amdgcn_readlane(q_hi, cc[h] & 63);
           pk2[h] = __builtin_amdgcn_readlane(q_pk, cc[h] & 63);
           gpar[h] = d == 0 ? 0.0f : ordered_to_float(ghi);
@@ -744,7 +1007,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
             list[base + (h ? kept[0] : 0) + lane_rank(em[h])] = ((uint64_t)ordered_bits(g2[h]) << 32) | lo;
             // the child's input projection (this member's three gate slices, a
             // line each) is fetched into L2 while the list is sorted
-            if (d + 1 < L) {
+            if (ARM == kCond && d + 1 < L) {
               const float *pr = a.P_all + (size_t)my_id * (3 * dh) + member * UW;
               pf[3 * h] = pr[0];
               pf[3 * h + 1] = pr[dh];
@@ -764,7 +1027,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
           *reinterpret_cast<f32x4 *>(gpart + (wave * 6 + g) * kTile + (lane >> 4) * 68 + (lane & 15) * 4) = acc[g];
       }
       // ... and the next depth's U rows (one line each)
-      if (wave == GW - 1 && d + 1 < L) pf[6] = a.U_all[(size_t)ids[(d + 1) * MP + lane] * dh + member * UW];
+      if (ARM == kCond && wave == GW - 1 && d + 1 < L) pf[6] = a.U_all[(size_t)ids[(d + 1) * MP + lane] * dh + member * UW];
       lds_barrier();
       const int nnew = __builtin_amdgcn_readfirstlane(ints[I_CNT0 + par]);
       par ^= 1;
@@ -900,11 +1163,11 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
     }
     prefetched();
     if (ints[I_STATUS] & DT_TREE_TIMEOUT) dead = true;
-    if (member != 0) {
+    if (ARM != kStatic && member != 0) {
       if (dead) return;  // (the others give up at their next wait)
       continue;
     }
-    // ---- emission (member 0) ------------------------------------------------------
+    // ---- emission (member 0; of a chain's tree, the member that built it) ------------------------------------------------------
     const int status = ints[I_STATUS];
     if (a.stats && tid == 0) {
       a.stats[2 * t] = nsteps;
@@ -976,23 +1239,30 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
 
 // The instance that takes d_h with `occ` workgroups per CU (null: none).  fp32
 // fragments take twice the registers, so they stay resident up to d_h = 256 only.
-const void *grow_fn(int wdt, int d_h, int occ) {
+template <int ARM>
+const void *grow_fn_arm(int wdt, int d_h, int occ) {
   if (wdt == DT_BF16) {
-    if (d_h == 64) return (const void *)grow_kernel<uint16_t, 1, 2, 2>;
-    if (d_h == 128) return (const void *)grow_kernel<uint16_t, 1, 4, 2>;
-    if (d_h == 256) return (const void *)grow_kernel<uint16_t, 2, 8, 2>;
+    if (d_h == 64) return (const void *)grow_kernel<uint16_t, 1, 2, 2, ARM>;
+    if (d_h == 128) return (const void *)grow_kernel<uint16_t, 1, 4, 2, ARM>;
+    if (d_h == 256) return (const void *)grow_kernel<uint16_t, 2, 8, 2, ARM>;
     if (d_h == 512)
-      return occ > 1 ? (const void *)grow_kernel<uint16_t, 4, 16, 2> : (const void *)grow_kernel<uint16_t, 4, 16, 1>;
-    return d_h < 512 ? (const void *)grow_kernel<uint16_t, 4, 0, 1> : nullptr;
+      return occ > 1 ? (const void *)grow_kernel<uint16_t, 4, 16, 2, ARM>
+                     : (const void *)grow_kernel<uint16_t, 4, 16, 1, ARM>;
+    return d_h < 512 ? (const void *)grow_kernel<uint16_t, 4, 0, 1, ARM> : nullptr;
   }
-  if (d_h == 64) return (const void *)grow_kernel<float, 1, 2, 2>;
-  if (d_h == 128) return (const void *)grow_kernel<float, 1, 4, 2>;
-  if (d_h == 256) return (const void *)grow_kernel<float, 2, 8, 2>;
-  return d_h < 256 ? (const void *)grow_kernel<float, 2, 0, 1> : nullptr;
+  if (d_h == 64) return (const void *)grow_kernel<float, 1, 2, 2, ARM>;
+  if (d_h == 128) return (const void *)grow_kernel<float, 1, 4, 2, ARM>;
+  if (d_h == 256) return (const void *)grow_kernel<float, 2, 8, 2, ARM>;
+  return d_h < 256 ? (const void *)grow_kernel<float, 2, 0, 1, ARM> : nullptr;
 }
+const void *grow_fn(int arm, int wdt, int d_h, int occ) {
+  if (arm == kMarg) return (const void *)grow_kernel<float, 1, 1, 2, kMarg>;  // (reads no weights)
+  return arm == kStatic ? grow_fn_arm<kStatic>(wdt, d_h, occ) : grow_fn_arm<kCond>(wdt, d_h, occ);
+}
+int grow_members(const dt_plan *p) { return p->scorer == kMarg ? 1 : p->d_h / UW; }
 
 // groups of workgroups resident at once with `occ` per CU
-int grow_most(const dt_plan *p, int occ) { return p->num_xcd * (occ * (p->num_cus / p->num_xcd) / (p->d_h / UW)); }
+int grow_most(const dt_plan *p, int occ) { return p->num_xcd * (occ * (p->num_cus / p->num_xcd) / grow_members(p)); }
 
 // One workgroup per CU while that gives every tree a group (more registers, and
 // nothing to share the CU with: 30.2 against 33.8 us for one tree at d_h = 512);
@@ -1004,16 +1274,16 @@ int grow_occ(const dt_plan *p, int batch) { return batch > grow_most(p, 1) && p-
 // Shapes whose menus and budgets fit a wave (M, B <= 64), whose scan lists the
 // register merge takes, and whose W_hh slices stay in registers.
 bool grow_fits(const dt_plan *p, int batch) {
-  return p->M <= 64 && p->B <= 64 && p->scorer == DT_SCORER_COND && p->frontier_w == 0 && p->grow_occ > 0 &&
+  return p->M <= 64 && p->B <= 64 && p->frontier_w == 0 && p->grow_occ > 0 &&
          sel::wave_merge_fits(scan_geom(batch * p->L, p->V, p->M).nchunks, p->M);
 }
 
 // how many workgroups of the kernel a CU can hold, at most 2 (0: the shape does not fit)
-int grow_max_occ(int wdt, int d_h, int L, int B, int num_cus, int num_xcd) {
-  if (d_h / UW > num_cus / num_xcd) return 0;
-  const int lds = grow_layout(L, B).total;
+int grow_max_occ(int arm, int wdt, int d_h, int L, int B, int num_cus, int num_xcd) {
+  if (arm != kMarg && d_h / UW > num_cus / num_xcd) return 0;
+  const int lds = grow_layout(L, B, arm).total;
   for (int occ = 2; occ > 0; --occ) {
-    const void *fn = grow_fn(wdt, d_h, occ);
+    const void *fn = grow_fn(arm, wdt, d_h, occ);
     int nb = 0;
     if (!fn) return 0;
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess &&
@@ -1025,6 +1295,7 @@ int grow_max_occ(int wdt, int d_h, int L, int B, int num_cus, int num_xcd) {
 }
 
 int grow_groups(const dt_plan *p, int batch) {
+  if (p->scorer == kMarg) return batch;  // (workgroups that wait for no other)
   const int most = grow_most(p, grow_occ(p, batch));
   return batch < most ? batch : most;
 }
@@ -1034,7 +1305,7 @@ size_t grow_state_bytes(const dt_plan *p, int batch) {
   return (size_t)grow_groups(p, batch) * 2 * CH * row;
 }
 size_t grow_part_bytes(const dt_plan *p, int batch) {
-  return (size_t)grow_groups(p, batch) * 3 * CH * (p->d_h / UW) * MP * sizeof(float);
+  return (size_t)grow_groups(p, batch) * 3 * CH * grow_members(p) * MP * sizeof(float);
 }
 
 hipError_t launch_grow(const dt_plan *p, int batch, const float *h0, float inv_tau, const Workspace &ws,
@@ -1046,7 +1317,7 @@ hipError_t launch_grow(const dt_plan *p, int batch, const float *h0, float inv_t
   a.M = p->M;
   a.B = p->B;
   a.k = p->k;
-  a.G = p->d_h / UW;
+  a.G = grow_members(p);
   a.norm_mode = p->norm_mode;
   a.pos_offset = p->pos_offset;
   a.batch = batch;
@@ -1075,8 +1346,8 @@ hipError_t launch_grow(const dt_plan *p, int batch, const float *h0, float inv_t
   a.stats = stats;
   a.cost = p->cost;
   a.out = *out;
-  const size_t lds = (size_t)grow_layout(p->L, p->B).total;
-  const void *fn = grow_fn(p->wdt, p->d_h, grow_occ(p, batch));
+  const size_t lds = (size_t)grow_layout(p->L, p->B, p->scorer).total;
+  const void *fn = grow_fn(p->scorer, p->wdt, p->d_h, grow_occ(p, batch));
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const int grid = a.nxcd * a.G * ((a.ngroups + a.nxcd - 1) / a.nxcd);

@@ -238,7 +238,7 @@ size_t expand_part_bytes(const dt_plan *p, int batch);
 // workspace and launch (compact: the rows are merged, and the tables hold a row
 // for every candidate slot, (t L + d) M + m, instead of the vocabulary)
 bool grow_fits(const dt_plan *p, int batch);
-int grow_max_occ(int wdt, int d_h, int L, int B, int num_cus, int num_xcd);
+int grow_max_occ(int arm, int wdt, int d_h, int L, int B, int num_cus, int num_xcd);
 int grow_groups(const dt_plan *p, int batch);
 size_t grow_state_bytes(const dt_plan *p, int batch);
 size_t grow_part_bytes(const dt_plan *p, int batch);

@@ -66,3 +66,37 @@ def test_plateau_order(B):
         assert key == sorted(key), key
         compare_tree(wl, t, got, dw.kw, name="plateau")
     dw.close()
+
+
+ARM_CASES = [c for c in CASES if c[0] not in ("budget_one", "cut_menus")] + [
+    ("budget_one_chain", 2, 3, 300, 64, 1, 1.0, 64, H, 0, True, 1, 2.0),
+    ("cut_menus_chain", 2, 4, 700, 64, 48, 1.0, 256, F, 3, True, 0, 0.3),
+    ("chains_in_rounds", 600, 3, 90, 8, 6, 1.0, 64, F, 0, True, 0, 1.0),
+    ("one_level", 3, 1, 300, 16, 16, 1.0, 128, H, 0, True, 0, 1.0),
+]
+
+
+@pytest.mark.parametrize("scorer", [1, 2], ids=["marg", "static"])
+@pytest.mark.parametrize("c", ARM_CASES, ids=[c[0] for c in ARM_CASES])
+def test_arms(c, scorer):
+    """The path-independent children functions: a marginal tree per workgroup, and the greedy chain
+    (its own exchange) with the trees built from its menus by the group's members."""
+    name, batch, L, V, M, B, T, d_h, dt, k, h0, norm, scale = c
+    print(f"[grow] {name} scorer {scorer}", flush=True)
+    wl = synth.random_small(len(name) + B, batch=batch, L=L, V=V, M=M, B=B, T=T, d_e=48, d_h=d_h, dtype=dt,
+                            h0=h0, logit_scale=scale, spikes=3, spike=3.0 * scale, w_scale=1.0 / np.sqrt(d_h))
+    x = wl.logits.copy()
+    bad = batch // 3 if batch > 2 else None  # a tree that cannot be built, beside ones that can
+    if bad is not None:
+        x[bad, 0, 3] = np.nan if dt == F else 0x7FC0
+    wl.logits = x
+    dw = DeviceWorkload(wl, max_children=k, norm_mode=norm, scorer=scorer)
+    got = dw.run()
+    again = dw.run()
+    for f in got:
+        np.testing.assert_array_equal(got[f], again[f], err_msg=f)
+    for t in sorted({0, batch // 2, batch - 1} - {bad}):
+        compare_tree(wl, t, got, dw.kw, name=name)
+    if bad is not None:
+        assert got["status"][bad] != 0 and got["n_nodes"][bad] == 0
+    dw.close()
