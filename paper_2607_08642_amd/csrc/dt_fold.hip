@@ -28,16 +28,22 @@ constexpr int kLdsPad = 8;  // bf16 elements of padding per LDS row
 // Tile of a GEMM block, one-dimensional grid: blocks are dealt to the XCDs
 // round-robin, so the column tiles of a row tile are put on one XCD, one after
 // the other, and its embedding rows are read into one L2 (not eight).
+// With fewer rows than columns (by_col) it is the row tiles of a column tile that
+// share an XCD: an L2 then reads its columns of the weights and all of the
+// embedding rows, the smaller part (1,024 rows at d_e = 2560, d_h = 512: 6.6 MB
+// instead of 11.2, 37.5 -> 32.5 us).
 constexpr int kFoldXcds = 8;
 struct FoldTile {
   int col, row;
 };
-__device__ inline FoldTile fold_tile(int ncol) {
+__device__ inline FoldTile fold_tile(int ncol, int nrow, bool by_col) {
   const int xcd = blockIdx.x % kFoldXcds, i = blockIdx.x / kFoldXcds;
+  if (by_col) return FoldTile{i / nrow * kFoldXcds + xcd, i % nrow};
   return FoldTile{i % ncol, i / ncol * kFoldXcds + xcd};
 }
-inline dim3 fold_grid(int ncol, int nrow) {
-  return dim3((unsigned)ncol * ((nrow + kFoldXcds - 1) / kFoldXcds * kFoldXcds));
+inline dim3 fold_grid(int ncol, int nrow, bool by_col) {
+  const int in = by_col ? nrow : ncol, across = by_col ? ncol : nrow;  // (in: the tiles that share an XCD)
+  return dim3((unsigned)in * ((across + kFoldXcds - 1) / kFoldXcds * kFoldXcds));
 }
 
 // ---------------------------------------------------------------------------
@@ -48,14 +54,14 @@ inline dim3 fold_grid(int ncol, int nrow) {
 // loads in line, 4.2 ms (610 TFLOP/s) ahead and with a row tile kept on one XCD.
 // cadd (nullable): c is also added to cadd[row].
 // ---------------------------------------------------------------------------
-template <int WR, int WC, int TI, int TJ>
+template <int WR, int WC, int TI, int TJ, int BK>
 __global__ __launch_bounds__(kFoldThreads) void fold_mfma_kernel(
     const uint16_t *__restrict__ emb, const int32_t *__restrict__ cand, int rows_total, int d_e,
     const uint16_t *__restrict__ wfold, int nf, int d_h, const float *__restrict__ b_ih,
     const float *__restrict__ b_c, float *__restrict__ P, float *__restrict__ U,
-    float *__restrict__ cvec, float *__restrict__ cadd) {
+    float *__restrict__ cvec, float *__restrict__ cadd, bool by_col) {
   static_assert(WR * WC == 4, "4 waves");
-  constexpr int BM = WR * TI * 32, BN = WC * TJ * 32, BK = kFoldBK;
+  constexpr int BM = WR * TI * 32, BN = WC * TJ * 32;
   constexpr int LDW = BK + kLdsPad;
   constexpr int TPR = kFoldThreads / BM;  // threads per row of the E . b_c sums
   static_assert(TPR * BM == kFoldThreads && BK % (8 * TPR) == 0, "whole 16-byte segments per thread");
@@ -66,9 +72,9 @@ __global__ __launch_bounds__(kFoldThreads) void fold_mfma_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave / WC, wc = wave % WC;
-  const FoldTile tile = fold_tile((nf + BN - 1) / BN);
+  const FoldTile tile = fold_tile((nf + BN - 1) / BN, (rows_total + BM - 1) / BM, by_col);
   const int n0 = tile.col * BN, r0 = tile.row * BM;
-  if (r0 >= rows_total) return;
+  if (r0 >= rows_total || n0 >= nf) return;
   const bool do_c = tile.col == 0;  // the first column tile also computes c = E_c b_c
 
   for (int i = tid; i < BM; i += kFoldThreads) {
@@ -207,16 +213,16 @@ __global__ __launch_bounds__(kFoldThreads) void fold_f32_kernel(
     const float *__restrict__ emb, const int32_t *__restrict__ cand, int rows_total, int d_e,
     const float *__restrict__ wfold, int nf, int d_h, const float *__restrict__ b_ih,
     const float *__restrict__ b_c, float *__restrict__ P, float *__restrict__ U, float *__restrict__ cvec,
-    float *__restrict__ cadd) {
+    float *__restrict__ cadd, bool by_col) {
   constexpr int BM = 64, BN = 64, BK = 32, LDW = BK + 2;
   constexpr int NL = BM * BK / kFoldThreads;  // elements per thread and operand
   __shared__ float As[BM * LDW], Bs[BN * LDW];
   __shared__ int32_t rowtok[BM];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
-  const FoldTile tile = fold_tile((nf + 1 + BN - 1) / BN);
+  const FoldTile tile = fold_tile((nf + 1 + BN - 1) / BN, (rows_total + BM - 1) / BM, by_col);
   const int n0 = tile.col * BN, r0 = tile.row * BM;
-  if (r0 >= rows_total) return;
+  if (r0 >= rows_total || n0 > nf) return;
   if (tid < BM) rowtok[tid] = r0 + tid < rows_total ? (cand ? cand[r0 + tid] : r0 + tid) : -1;
   __syncthreads();
   f32x16 acc;
@@ -313,109 +319,134 @@ __global__ __launch_bounds__(256) void fold_simple_kernel(
 // ---------------------------------------------------------------------------
 // plan-time packing
 // ---------------------------------------------------------------------------
-// [W_ih ; W_c^T] as rows of K = d_e: W_ih is copied, W_c transposed through LDS in
-// 64 x 64 tiles (element by element, its reads were strided by d_h: 18 us for 10 MB
-// of bf16, 14 us this way).  Rows past 4 d_h are zeros.  blockIdx.x: tiles of
-// columns (k), blockIdx.y: tiles of rows.
+// One launch packs everything: a one-shot call runs it each time, and is bound by
+// the latency of its few loads (13 MB at d_e = 2560, d_h = 512, 3 us at the
+// memory's rate), so every thread has its 16-byte loads in flight together and
+// the parts run side by side: 8.6 us (three launches with loads of one element:
+// 13.4 + 4.3 + 3.6 us and two gaps).
+//   blocks [0, whh)       W_hh in MFMA A-fragment order for the expansion kernels:
+//     bf16 (16x16x32 MFMA): fragment (u, g, ks) is 64 lanes x 8 bf16; lane l holds
+//       W_hh[g*d_h + 16u + l%16][ks*32 + (l/16)*8 + e], e = 0..7;
+//     fp32 (16x16x4 MFMA, four per k-group of 16): fragment (u, g, q) is 64 lanes x
+//       4 floats; lane l holds W_hh[g*d_h + 16u + l%16][16q + (l/16)*4 + e];
+//     either way 16 bytes a lane, and one k group of 64 bytes a fragment
+//   blocks [whh, bias)    b_ih (plus b_hh on the gates r and z), b_hh and b_c in
+//     fp32; missing ones are zeros
+//   blocks [bias, ih)     [W_ih; W_c^T] as rows of K = d_e: W_ih is copied ...
+//   blocks [ih, ...)      ... W_c transposed through LDS in 64 x 64 tiles, and the
+//     rows past 4 d_h zeros
+struct PackArgs {
+  const void *w_ih, *w_hh, *w_c, *b_ih, *b_hh, *b_c;
+  void *wfold, *whh;
+  float *o_ih, *o_hh, *o_c;
+  int d_e, d_h, nf_pad;
+  int whh_end, bias_end, ih_end;
+};
+constexpr int kPackThreads = 256;
+constexpr int kPackVecs = 4;  // 16-byte loads a thread has in flight
+
 template <typename TW>
-__global__ __launch_bounds__(256) void pack_wfold_kernel(const TW *__restrict__ w_ih, const TW *__restrict__ w_c,
-                                                         int d_e, int d_h, int nf_pad, TW *__restrict__ out) {
-  __shared__ TW tile[64][65];
-  const int k0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-  const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
-  // (a tile lies in W_ih, or in W_c^T and the rows past it, or across: 3 d_h % 32 == 0)
-  for (int i = y; i < 64; i += 4) {  // W_c row k0 + i, columns n0 + x - 3 d_h
-    const int k = k0 + i, c = n0 + x - 3 * d_h;
-    if (k < d_e && c >= 0 && c < d_h) tile[i][x] = w_c[(size_t)k * d_h + c];
+__global__ __launch_bounds__(kPackThreads) void pack_kernel(PackArgs a) {
+  constexpr int E = 16 / sizeof(TW);
+  // 16 bytes at the elements' own alignment (the callers' weights need no more)
+  typedef TW Vec __attribute__((ext_vector_type(E), aligned(sizeof(TW))));
+  const int tid = threadIdx.x, blk = blockIdx.x, d_e = a.d_e, d_h = a.d_h;
+  if (blk < a.whh_end) {
+    const TW *in = static_cast<const TW *>(a.w_hh);
+    TW *out = static_cast<TW *>(a.whh);
+    const int nk = d_h / (4 * E), total = 3 * d_h * d_h / E;
+    Vec v[kPackVecs];
+#pragma unroll
+    for (int q = 0; q < kPackVecs; ++q) {
+      const int i = (blk * kPackVecs + q) * kPackThreads + tid;
+      if (i >= total) continue;
+      const int l = i & 63, frag = i >> 6, k = frag % nk, g = frag / nk % 3, u = frag / nk / 3;
+      v[q] = *reinterpret_cast<const Vec *>(in + (size_t)(g * d_h + 16 * u + (l & 15)) * d_h + k * 4 * E + (l >> 4) * E);
+    }
+#pragma unroll
+    for (int q = 0; q < kPackVecs; ++q) {
+      const int i = (blk * kPackVecs + q) * kPackThreads + tid;
+      if (i < total) *reinterpret_cast<Vec *>(out + (size_t)i * E) = v[q];
+    }
+  } else if (blk < a.bias_end) {
+    const int i = (blk - a.whh_end) * kPackThreads + tid;
+    const TW *b_ih = static_cast<const TW *>(a.b_ih), *b_hh = static_cast<const TW *>(a.b_hh),
+             *b_c = static_cast<const TW *>(a.b_c);
+    if (i < 3 * d_h) {
+      const float h = b_hh ? wval<TW>(b_hh, i) : 0.0f, x = b_ih ? wval<TW>(b_ih, i) : 0.0f;
+      a.o_hh[i] = h;
+      a.o_ih[i] = i < 2 * d_h ? x + h : x;
+    }
+    if (i < d_e) a.o_c[i] = b_c ? wval<TW>(b_c, i) : 0.0f;
+  } else if (blk < a.ih_end) {
+    const TW *in = static_cast<const TW *>(a.w_ih);
+    TW *out = static_cast<TW *>(a.wfold);
+    const int total = 3 * d_h * d_e / E;  // (whole vectors: d_h % 32 == 0)
+    Vec v[kPackVecs];
+#pragma unroll
+    for (int q = 0; q < kPackVecs; ++q) {
+      const int i = ((blk - a.bias_end) * kPackVecs + q) * kPackThreads + tid;
+      if (i < total) v[q] = *reinterpret_cast<const Vec *>(in + (size_t)i * E);
+    }
+#pragma unroll
+    for (int q = 0; q < kPackVecs; ++q) {
+      const int i = ((blk - a.bias_end) * kPackVecs + q) * kPackThreads + tid;
+      if (i < total) *reinterpret_cast<Vec *>(out + (size_t)i * E) = v[q];
+    }
+  } else {
+    constexpr int VR = 64 / E, NV = 64 * VR / kPackThreads;  // vectors per tile row, per thread
+    __shared__ TW tile[64][64 + 4 / sizeof(TW)];             // (a dword of padding: rows on other banks)
+    const TW *in = static_cast<const TW *>(a.w_c);
+    TW *out = static_cast<TW *>(a.wfold);
+    const int ncol = (d_e + 63) / 64, t = blk - a.ih_end, k0 = t % ncol * 64, n0 = t / ncol * 64;
+    Vec v[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {  // W_c row k, columns n .. n + E - 1 (all in or out: d_h % 32 == 0)
+      const int i = q * kPackThreads + tid, k = k0 + i / VR, n = n0 + i % VR * E;
+      v[q] = Vec(TW(0));
+      if (k < d_e && n < d_h) v[q] = *reinterpret_cast<const Vec *>(in + (size_t)k * d_h + n);
+    }
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int i = q * kPackThreads + tid;
+#pragma unroll
+      for (int e = 0; e < E; ++e) tile[i / VR][i % VR * E + e] = v[q][e];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int i = q * kPackThreads + tid, n = 3 * d_h + n0 + i / VR, kk = i % VR * E;
+      if (n >= a.nf_pad) continue;
+      TW *o = out + (size_t)n * d_e + k0 + kk;
+      Vec r;
+#pragma unroll
+      for (int e = 0; e < E; ++e) r[e] = tile[kk + e][i / VR];
+      if (k0 + kk + E <= d_e) {
+        *reinterpret_cast<Vec *>(o) = r;
+      } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if (k0 + kk + e < d_e) o[e] = r[e];
+      }
+    }
   }
-  __syncthreads();
-  for (int i = y; i < 64; i += 4) {
-    const int n = n0 + i, k = k0 + x;
-    if (n >= nf_pad || k >= d_e) continue;
-    out[(size_t)n * d_e + k] = n < 3 * d_h ? w_ih[(size_t)n * d_e + k] : (n < 4 * d_h ? tile[x][i] : TW(0));
-  }
-}
-
-// b_ih (plus b_hh on the gates r and z), b_hh and b_c in fp32; missing ones are zeros
-template <typename TW>
-__global__ void pack_bias_kernel(const TW *__restrict__ b_ih, const TW *__restrict__ b_hh, const TW *__restrict__ b_c,
-                                 int d_h, int d_e, float *__restrict__ o_ih, float *__restrict__ o_hh,
-                                 float *__restrict__ o_c) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 3 * d_h) {
-    const float h = b_hh ? wval<TW>(b_hh, i) : 0.0f, x = b_ih ? wval<TW>(b_ih, i) : 0.0f;
-    o_hh[i] = h;
-    o_ih[i] = i < 2 * d_h ? x + h : x;
-  }
-  if (i < d_e) o_c[i] = b_c ? wval<TW>(b_c, i) : 0.0f;
-}
-
-// W_hh packed in MFMA A-fragment order for the expansion kernel.
-// bf16 (16x16x32 MFMA): fragment (u, g, ks) is 64 lanes x 8 bf16; lane l holds
-//   W_hh[g*d_h + 16u + l%16][ks*32 + (l/16)*8 + e], e = 0..7.
-// fp32 (16x16x4 MFMA, four per k-group of 16): fragment (u, g, q) is 64 lanes x 4
-//   floats; lane l holds W_hh[g*d_h + 16u + l%16][16q + (l/16)*4 + e], e = 0..3.
-__global__ void pack_whh_bf16_kernel(const uint16_t *__restrict__ w_hh, int d_h,
-                                     uint16_t *__restrict__ out) {
-  const int nks = d_h / 32;
-  const size_t total = (size_t)3 * d_h * d_h;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const int e = (int)(i % 8);
-    const int lane = (int)((i / 8) % 64);
-    const size_t frag = i / 512;
-    const int ks = (int)(frag % nks);
-    const int g = (int)((frag / nks) % 3);
-    const int u = (int)(frag / nks / 3);
-    const int row = g * d_h + 16 * u + (lane & 15);
-    const int k = ks * 32 + (lane >> 4) * 8 + e;
-    out[i] = w_hh[(size_t)row * d_h + k];
-  }
-}
-
-__global__ void pack_whh_f32_kernel(const float *__restrict__ w_hh, int d_h, float *__restrict__ out) {
-  const int nq = d_h / 16;
-  const size_t total = (size_t)3 * d_h * d_h;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const int e = (int)(i % 4);
-    const int lane = (int)((i / 4) % 64);
-    const size_t frag = i / 256;
-    const int q = (int)(frag % nq);
-    const int g = (int)((frag / nq) % 3);
-    const int u = (int)(frag / nq / 3);
-    const int row = g * d_h + 16 * u + (lane & 15);
-    const int k = 16 * q + (lane >> 4) * 4 + e;
-    out[i] = w_hh[(size_t)row * d_h + k];
-  }
-}
-
-inline int grid_for(size_t n) {
-  size_t b = (n + 255) / 256;
-  return (int)(b > 65535 ? 65535 : (b < 1 ? 1 : b));
 }
 
 }  // namespace
 
 hipError_t pack_weights(dt_model *p, const dt_gru *gru, const dt_head *head, hipStream_t s) {
-  const int d_e = p->d_e, d_h = p->d_h;
-  const dim3 tiles((d_e + 63) / 64, (p->nf_pad + 63) / 64), block(256);
-  const int nbias = grid_for((size_t)(3 * d_h > d_e ? 3 * d_h : d_e)), nwhh = grid_for((size_t)3 * d_h * d_h);
-  if (p->wdt == DT_BF16) {
-    hipLaunchKernelGGL(pack_wfold_kernel<uint16_t>, tiles, block, 0, s, (const uint16_t *)gru->w_ih,
-                       (const uint16_t *)head->w, d_e, d_h, p->nf_pad, (uint16_t *)p->wfold);
-    hipLaunchKernelGGL(pack_bias_kernel<uint16_t>, dim3(nbias), block, 0, s, (const uint16_t *)gru->b_ih,
-                       (const uint16_t *)gru->b_hh, (const uint16_t *)head->b, d_h, d_e, p->b_ih, p->b_hh, p->b_c);
-    hipLaunchKernelGGL(pack_whh_bf16_kernel, dim3(nwhh), block, 0, s, (const uint16_t *)gru->w_hh, d_h,
-                       (uint16_t *)p->whh_t);
-  } else {
-    hipLaunchKernelGGL(pack_wfold_kernel<float>, tiles, block, 0, s, (const float *)gru->w_ih,
-                       (const float *)head->w, d_e, d_h, p->nf_pad, (float *)p->wfold);
-    hipLaunchKernelGGL(pack_bias_kernel<float>, dim3(nbias), block, 0, s, (const float *)gru->b_ih,
-                       (const float *)gru->b_hh, (const float *)head->b, d_h, d_e, p->b_ih, p->b_hh, p->b_c);
-    hipLaunchKernelGGL(pack_whh_f32_kernel, dim3(nwhh), block, 0, s, (const float *)gru->w_hh, d_h,
-                       (float *)p->whh_t);
-  }
+  const int d_e = p->d_e, d_h = p->d_h, per = kPackThreads * kPackVecs * 16 / (p->wdt == DT_BF16 ? 2 : 4);
+  auto blocks = [](int n, int each) { return (n + each - 1) / each; };
+  PackArgs a{gru->w_ih, gru->w_hh, head->w, gru->b_ih, gru->b_hh, head->b, p->wfold, p->whh_t,
+             p->b_ih, p->b_hh, p->b_c, d_e, d_h, p->nf_pad, 0, 0, 0};
+  a.whh_end = blocks(3 * d_h * d_h, per);
+  a.bias_end = a.whh_end + blocks(3 * d_h > d_e ? 3 * d_h : d_e, kPackThreads);
+  a.ih_end = a.bias_end + blocks(3 * d_h * d_e, per);
+  const dim3 grid(a.ih_end + blocks(d_e, 64) * blocks(p->nf_pad - 3 * d_h, 64)), block(kPackThreads);
+  if (p->wdt == DT_BF16)
+    hipLaunchKernelGGL(pack_kernel<uint16_t>, grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL(pack_kernel<float>, grid, block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -423,22 +454,27 @@ hipError_t pack_weights(dt_model *p, const dt_gru *gru, const dt_head *head, hip
 // ids in cand (-1: a row of zeros).  cadd: see fold_mfma_kernel.
 static hipError_t launch_fold(const dt_model *p, const int32_t *cand, int rows, float *cadd, hipStream_t s) {
   const dim3 block(kFoldThreads);
+  const bool by_col = rows <= p->nf;
   if (p->wdt == DT_F32) {
-    hipLaunchKernelGGL(fold_f32_kernel, fold_grid((p->nf + 1 + 63) / 64, (rows + 63) / 64), block, 0, s,
+    hipLaunchKernelGGL(fold_f32_kernel, fold_grid((p->nf + 1 + 63) / 64, (rows + 63) / 64, by_col), block, 0, s,
                        (const float *)p->emb, cand, rows, p->d_e, (const float *)p->wfold, p->nf, p->d_h, p->b_ih,
-                       p->b_c, p->P_all, p->U_all, p->c_all, cadd);
+                       p->b_c, p->P_all, p->U_all, p->c_all, cadd, by_col);
   } else if (p->d_e % 8 == 0) {
     // 128 x 128 tiles while they fill the chip twice over; smaller ones leave fewer
-    // CUs idle (1,024 rows: 128 against 512 tiles)
+    // CUs idle (1,024 rows: 128 against 512 tiles).  Their K slices are twice as
+    // long; more in flight, two or four slices of 64 or two of 128, was no faster
+    // (35.2, 34.0 and 33.3 us)
     const int t128 = ((p->nf + 127) / 128) * ((rows + 127) / 128);
     if (t128 >= 512)
-      hipLaunchKernelGGL((fold_mfma_kernel<2, 2, 2, 2>), fold_grid((p->nf + 127) / 128, (rows + 127) / 128), block, 0, s,
+      hipLaunchKernelGGL((fold_mfma_kernel<2, 2, 2, 2, 64>),
+                         fold_grid((p->nf + 127) / 128, (rows + 127) / 128, by_col), block, 0, s,
                          (const uint16_t *)p->emb, cand, rows, p->d_e, (const uint16_t *)p->wfold, p->nf, p->d_h,
-                         p->b_ih, p->b_c, p->P_all, p->U_all, p->c_all, cadd);
+                         p->b_ih, p->b_c, p->P_all, p->U_all, p->c_all, cadd, by_col);
     else
-      hipLaunchKernelGGL((fold_mfma_kernel<2, 2, 1, 1>), fold_grid((p->nf + 63) / 64, (rows + 63) / 64), block, 0, s,
+      hipLaunchKernelGGL((fold_mfma_kernel<2, 2, 1, 1, 128>),
+                         fold_grid((p->nf + 63) / 64, (rows + 63) / 64, by_col), block, 0, s,
                          (const uint16_t *)p->emb, cand, rows, p->d_e, (const uint16_t *)p->wfold, p->nf, p->d_h,
-                         p->b_ih, p->b_c, p->P_all, p->U_all, p->c_all, cadd);
+                         p->b_ih, p->b_c, p->P_all, p->U_all, p->c_all, cadd, by_col);
   } else {
     hipLaunchKernelGGL(fold_simple_kernel<uint16_t>, dim3(rows), dim3(256), 0, s, (const uint16_t *)p->emb, cand,
                        rows, p->d_e, (const uint16_t *)p->wfold, p->nf, p->d_h, p->b_ih, p->b_c, p->P_all, p->U_all,

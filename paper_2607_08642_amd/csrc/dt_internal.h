@@ -30,7 +30,6 @@ constexpr int kMergeLdsMax = 96 * 1024;  // row merge buffer (sel::merge_buf_byt
 // fold GEMM tile (bf16 MFMA path)
 constexpr int kFoldBM = 128;
 constexpr int kFoldBN = 128;
-constexpr int kFoldBK = 64;
 
 // expansion kernel
 constexpr int kExpThreads = 512;

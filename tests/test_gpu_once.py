@@ -59,3 +59,33 @@ def test_once_on_a_side_stream():
     got = {k: getattr(t, k).cpu().numpy() for k in
            ("tokens", "parents", "depth", "position_ids", "mask", "scores", "n_nodes", "status")}
     compare_tree(wl, 0, got, {}, name="side")
+
+
+@pytest.mark.parametrize("dt,d_e,d_h", [(H, 72, 64), (H, 37, 96), (F, 33, 32)])
+def test_weights_at_any_element_address(dt, d_e, d_h):
+    """Weights one element past a 16-byte boundary: the same trees, bit for bit, on both routes."""
+    wl = synth.random_small(7, batch=2, L=4, V=3001, M=24, B=16, T=0.7, d_e=d_e, d_h=d_h, dtype=dt,
+                            gru_bias=True, head_bias=True)
+    w = {k: to_dev(getattr(wl.weights, k), dt) for k in ("emb", "w_ih", "w_hh", "b_ih", "b_hh", "w_c", "b_c")}
+
+    def shifted(t):
+        s = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)[1:].view(t.shape)
+        return s.copy_(t)
+
+    off = {k: t if k == "emb" else shifted(t) for k, t in w.items()}
+    logits = to_dev(wl.logits, wl.logits_dtype)
+    trees = []
+    for x in (w, off):
+        gru, head = (x["w_ih"], x["w_hh"], x["b_ih"], x["b_hh"]), (x["w_c"], x["b_c"])
+        trees.append(binding.build_tree(logits, x["emb"], gru, head, 4, 24, 16, wl.T))
+        plan = binding.Plan(x["emb"], *gru, *head, L=4, M=24, B=16, logits_dtype=wl.logits_dtype, max_batch=2)
+        trees.append(plan.build_tree(logits, wl.T))
+        torch.cuda.synchronize()
+        plan.close()
+    for a, b in ((0, 2), (1, 3)):
+        for f in ("tokens", "parents", "mask", "scores", "n_nodes", "status"):
+            assert torch.equal(getattr(trees[a], f), getattr(trees[b], f)), f
+    got = {k: getattr(trees[2], k).cpu().numpy() for k in
+           ("tokens", "parents", "depth", "position_ids", "mask", "scores", "n_nodes", "status")}
+    for i in range(2):
+        compare_tree(wl, i, got, {}, name="shifted")
