@@ -621,7 +621,8 @@ static dt_status once_plan(dt_plan *p, int V, int d_e, int d_h, int weights_dtyp
   if (e != hipSuccess) return hip_fail(e, "device query");
   st = plan_init(p, V, d_e, d_h, weights_dtype, dev, L, M, B, logits_dtype, batch, opts);
   if (st != DT_OK) return st;
-  if ((long long)batch * L * M >= V || !dt::grow_fits(p, batch))
+  // (the arms: Marg needs no fold and must not take E b_c; neither is worth a route here)
+  if ((long long)batch * L * M >= V || p->scorer != DT_SCORER_COND || !dt::grow_fits(p, batch))
     return fail(DT_ERR_UNSUPPORTED, "a one-shot call of this shape needs a plan (dt_plan_create)");
   return DT_OK;
 }

@@ -22,6 +22,8 @@ CASES = [
     ("vocabulary", 4, 4, 300, 32, 16, 64, 64, F, True, True, {}),           # batch L M >= V: a plan
     ("wide", 1, 3, 4000, 96, 16, 64, 64, H, False, False, {}),              # M > 64: a plan
     ("marg", 1, 3, 4000, 16, 16, 64, 64, F, False, False, dict(scorer=1)),  # another arm: a plan
+    ("marg_bias", 1, 3, 4000, 16, 16, 64, 64, F, True, True, dict(scorer=1)),  # (no E b_c in marginal menus)
+    ("static_bias", 2, 3, 4000, 16, 16, 64, 64, F, True, True, dict(scorer=2)),
 ]
 
 
