@@ -884,6 +884,11 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
         if (xbuf == 0) ncb[0] = nc;
         if (xbuf == 1) ncb[1] = nc;
         if (xbuf == 2) ncb[2] = nc;
+      } else if constexpr (ARM != kCond) {
+        // the last step's count and children are read by every wave behind that
+        // step's one barrier and written anew below (a conditional step's barriers
+        // above stand between the two)
+        lds_barrier();
       }
       if (tid == 0) ints[I_CNT0 + (par ^ 1)] = 0;
       // 4. children: nodes wave, wave + 4, ... (pairs); lane = slot

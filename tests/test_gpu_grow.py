@@ -100,3 +100,23 @@ def test_arms(c, scorer):
     if bad is not None:
         assert got["status"][bad] != 0 and got["n_nodes"][bad] == 0
     dw.close()
+
+
+@pytest.mark.parametrize("scorer", [1, 2], ids=["marg", "static"])
+def test_arm_copies_agree(scorer):
+    """Two trees of many short steps (a child count and a few children read and written anew in each),
+    768 copies of each side by side: every copy is the same tree, and the oracle's."""
+    wl = synth.random_small(21, batch=2, L=24, V=150, M=8, B=64, T=1.0, d_e=32, d_h=64, dtype=F, h0=True,
+                            logit_scale=1.0, spikes=2, spike=9.0, w_scale=0.125)
+    n = 768
+    wl.logits, wl.h0, wl.batch = np.tile(wl.logits, (n, 1, 1)), np.tile(wl.h0, (n, 1)), 2 * n
+    print(f"[grow] copies scorer {scorer}", flush=True)
+    dw = DeviceWorkload(wl, max_children=2, scorer=scorer)
+    for _ in range(4):
+        got = dw.run()
+        for f in got:
+            pair = got[f].reshape(n, 2, -1)
+            np.testing.assert_array_equal(pair, np.broadcast_to(pair[:1], pair.shape), err_msg=f)
+    for t in (0, 1):
+        compare_tree(wl, t, got, dw.kw, name="copies")
+    dw.close()
