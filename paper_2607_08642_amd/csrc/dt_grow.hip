@@ -13,13 +13,17 @@
 //    itself: no node table, no append, no second ranking pass.
 //  * The list's order is the heap's pop order, ties included, so the final list
 //    is the emitted tree and no replay follows.  Nodes are ordered by
-//      (score desc, level asc, parent's place asc, slot asc),
+//      (score desc, level asc, parent's place asc, sibling's rank),
 //    level = how many of its nearest ancestors share the node's score in
 //    unbroken succession.  Among nodes of one score the heap works first in,
 //    first out (equal keys leave by insertion order, and all of those whose
 //    parents score higher are in before the first leaves): level by level, and
-//    within a level by the parents' order, then the siblings' rank.  An ancestor
-//    always precedes its descendants, so cutting the list at B keeps parents.
+//    within a level by the parents' order, then the siblings' rank (log-prob desc,
+//    slot asc).  Siblings of one score are rare -- twins, or log-probs that the sum
+//    with a low parent's score rounds together -- so entries carry their slot as the
+//    rank, and a step whose list holds such siblings ranks its nodes' children and
+//    sorts again.  An ancestor always precedes its descendants, so cutting the list
+//    at B keeps parents.
 //  * A member owns 32 hidden units (G = d_h / 32 members) and keeps its W_hh
 //    fragments in registers for the whole launch; two workgroups can share a CU.
 //    With more trees than resident groups a group builds several in turn.
@@ -429,6 +433,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
   float *gh = reinterpret_cast<float *>(smem + ly.gh);
   uint64_t *ancs = reinterpret_cast<uint64_t *>(smem + ly.anc);
   float2 *red = reinterpret_cast<float2 *>(smem + ly.red);
+  uint64_t *cut = reinterpret_cast<uint64_t *>(smem + ly.red);  // (the row merges are done by then)
   int *ints = reinterpret_cast<int *>(smem + ly.ints);
   int32_t *ids = reinterpret_cast<int32_t *>(smem + ly.ids);
   float *vals = reinterpret_cast<float *>(smem + ly.vals);
@@ -762,8 +767,9 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
 
     // ---- the candidate list: lane i holds entry i -----------------------------
     // hi: order-preserving score bits; lo: the rest of the order, (63 - level) << 26
-    // | (126 - parent's place) << 19 | (63 - slot) << 13 (the root's children: 127);
-    // meta: depth | expanded << 7 | parent's state slot << 8 | state slot << 16
+    // | (126 - parent's place) << 19 | (63 - sibling's rank) << 13 (the root's children:
+    // 127), and slot << 6; meta: depth | expanded << 7 | parent's state slot << 8 |
+    // state slot << 16
     uint32_t e_hi = 0, e_lo = 0, e_meta = 0;
     int n = 0;
     float vB = NEG_INF;
@@ -1008,7 +1014,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
             const int level = d > 0 && g2[h] == gpar[h] ? (int)((pk2[h] >> 20) & 63) + 1 : 0;
             const uint32_t place = d == 0 ? 0u : (pk2[h] & 63u) + 1u;  // parent's place + 1
             const uint32_t lo = ((uint32_t)(63 - min(level, 63)) << 26) | ((127u - place) << 19) |
-                                ((uint32_t)(63 - slot) << 13) | 0x1000u | (uint32_t)cc[h];
+                                ((uint32_t)(63 - slot) << 13) | 0x1000u | ((uint32_t)slot << 6) | (uint32_t)cc[h];
             list[base + (h ? kept[0] : 0) + lane_rank(em[h])] = ((uint64_t)ordered_bits(g2[h]) << 32) | lo;
             // the child's input projection (this member's three gate slices, a
             // line each) is fetched into L2 while the list is sorted
@@ -1085,10 +1091,11 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
       }
       if (corr) xpar ^= 1;
       // 5. the new list: the best of the old entries (payload: their lane) and the
-      // children (payload: 0x1000 | chunk node)
+      // children (payload: 0x1000 | slot << 6 | chunk node)
       const int total = n + nnew;
       uint32_t k = e_hi, p = e_lo | (uint32_t)lane;
       if (lane >= n) k = p = 0u;
+      bool tie = false;  // new siblings of one score, in slot order
       if (total <= 64) {
         if (lane >= n && lane < total) {
           const uint64_t e = list[lane - n];
@@ -1103,12 +1110,17 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
         if (__ballot(lane < total && ks == 0) != 0) {
           at = count_above(((uint64_t)k << 32) | p, total);
           ks = push((int)k, at);
+          if constexpr (ARM != kMarg) {
+            const uint32_t ps = push((int)p, at), pn = pull((int)ps, lane + 1);
+            tie = lane + 1 < total && (uint32_t)pull((int)ks, lane + 1) == ks && (pn >> 19) == (ps >> 19) && (ps & 0x1000u);
+          }
         }
         p = push((int)p, at);
         k = ks;
       } else {
         // too many for a lane each: wave 0 adds the old entries, every thread ranks
-        // its share among all of them, and the best meet in LDS
+        // its share among all of them, and the best meet in LDS (the first beyond
+        // them beside, to be seen as a sibling of the last)
         if (wave == 0 && lane < n) list[nnew + lane] = ((uint64_t)k << 32) | p;
         lds_barrier();
         for (int i = tid; i < total; i += GT) {
@@ -1122,9 +1134,87 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
           }
           if (total & 1) at += list[total - 1] > e;
           if (at < B) top[at] = e;
+          if (ARM != kMarg && at == B) *cut = e;
         }
         lds_barrier();
         const uint64_t e = lane < B ? top[lane] : 0ull;  // (total > 64 >= B: all of them are there)
+        k = (uint32_t)(e >> 32);
+        p = (uint32_t)e;
+        if constexpr (ARM != kMarg) {
+          const uint64_t en = lane + 1 < B ? top[lane + 1] : *cut;
+          tie = lane < B && (e >> 19) == (en >> 19) && (p & 0x1000u);
+        }
+      }
+      // (the root's children: score = log-prob, so slots order the equal ones; a
+      // marginal menu's log-probs descend with the slot)
+      if (__builtin_expect(ARM != kMarg && d > 0 && __ballot(tie) != 0, 0)) {
+        // The children by their log-probs' order, formed from their values again.  The
+        // partial corrections stay until every member has sent the next ones; the
+        // ranks go where the nodes' states were, which nothing reads any more in this
+        // step.  A chain's menu is one for all nodes.  (Opaque, as above: nothing of
+        // this is kept in registers over the loop; without it, and as a second pass
+        // through the code above, a call took 2-6% longer.)
+        int lane_ = lane0;
+        asm volatile("" : "+v"(lane_));
+        const int lane = lane_, tid = wave * 64 + lane, slot = 4 * (lane & 15) + (lane >> 4);
+        uint8_t *rk = reinterpret_cast<uint8_t *>(Sn);  // [CH][MP] (a conditional tree's)
+        static_assert(CH * MP <= CH * SNS * 4, "the ranks fit the states");
+        if constexpr (ARM == kCond) {
+#pragma unroll 1
+          for (int c = wave; c < nc; c += GW) {
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            const int base = part_off(xbuf == 0 ? 2 : xbuf - 1, c, 0) + lane * 16;
+#pragma unroll 1
+            for (int j = 0; j + (lane >> 4) < G; j += 4) {
+              const uint4 w = ld16(rpart, base + j * (MP * 4));
+              s.x += as_f(w.x);
+              s.y += as_f(w.y);
+              s.z += as_f(w.z);
+              s.w += as_f(w.w);
+            }
+            const float v = vals[d * MP + slot] + fold16(fold32(s.x, s.z), fold32(s.y, s.w));
+            const uint64_t key = ((uint64_t)ordered_bits(v) << 32) | (uint32_t)(63 - slot);
+            int r = 63;
+#pragma unroll 1
+            for (int j = 0; j < 64; ++j) {
+              const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)key, j);
+              const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), j);
+              r -= (((uint64_t)hi << 32) | lo) > key;
+            }
+            rk[c * MP + slot] = (uint8_t)r;
+          }
+        }
+        lds_barrier();
+        // ... and the list sorted again, every thread its share
+        if (wave == 0 && lane < n) list[nnew + lane] = ((uint64_t)e_hi << 32) | e_lo | (uint32_t)lane;
+        for (int i = tid; i < nnew; i += GT) {
+          const uint64_t e = list[i];
+          uint32_t r;
+          if constexpr (ARM == kCond) {
+            r = rk[((uint32_t)e & 15u) * MP + (((uint32_t)e >> 6) & 63u)];
+          } else {
+            const int sl = ((uint32_t)e >> 6) & 63u;
+            const float v = vals[d * MP + sl];
+            r = 63;
+#pragma unroll 1
+            for (int j = 0; j < 64; ++j) {
+              const float o = vals[d * MP + j];
+              r -= o > v || (o == v && j < sl);
+            }
+          }
+          list[i] = (e & ~(63ull << 13)) | (r << 13);
+        }
+        lds_barrier();
+#pragma unroll 1
+        for (int i = tid; i < total; i += GT) {
+          const uint64_t e = list[i];
+          int at = 0;
+#pragma unroll 1
+          for (int j = 0; j < total; ++j) at += list[j] > e;
+          if (at < B) top[at] = e;
+        }
+        lds_barrier();
+        const uint64_t e = lane < B && lane < total ? top[lane] : 0ull;
         k = (uint32_t)(e >> 32);
         p = (uint32_t)e;
       }
@@ -1139,7 +1229,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
       const int pnew = pull(np, place ? (int)place - 1 : 0);
       const uint32_t nplace = place ? (uint32_t)pnew + 1u : 0u;
       e_hi = live ? k : 0u;
-      e_lo = (p & 0xFC07E000u) | ((127u - nplace) << 19);
+      e_lo = (p & 0xFC07EFC0u) | ((127u - nplace) << 19);
       e_meta = isnew ? (d + 1) | ((sbase + scount + (int)(p & 15u)) << 8) : om;
       vB = n == B ? ordered_to_float(__builtin_amdgcn_readlane(k, B - 1)) : NEG_INF;
       // 6. the next chunk: up to 16 unexpanded nodes of the least depth, best first
@@ -1162,8 +1252,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
       nexp += nc;
       const int dst = mine_ ? before : 63;  // (lanes nc .. hold nothing)
       q_hi = push(e_hi, dst);
-      q_pk = push(lane | ((63 - ((e_lo >> 13) & 63)) << 6) | (((e_meta >> 8) & 255) << 12) |
-                      ((63 - (e_lo >> 26)) << 20), dst);
+      q_pk = push(lane | (e_lo & 0xFC0u) | (((e_meta >> 8) & 255) << 12) | ((63 - (e_lo >> 26)) << 20), dst);
       if (mine_) e_meta |= 128 | ((sbase + scount + before) << 16);
     }
     prefetched();
@@ -1211,7 +1300,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
       }
     }
     if (wave == 0) {
-      const int dep = e_meta & 127, m = 63 - (int)((e_lo >> 13) & 63u);
+      const int dep = e_meta & 127, m = (int)((e_lo >> 6) & 63u);
       if (lane < B) {
         otok[lane] = !emit ? -1 : a.compact ? a.cand[ids[(dep - 1) * MP + m]] : ids[(dep - 1) * MP + m];
         opar[lane] = parent;

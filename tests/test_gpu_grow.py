@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from gpu_util import DeviceWorkload, compare_tree
+from helpers import run_oracle
 from paper_2607_08642_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -120,3 +121,52 @@ def test_arm_copies_agree(scorer):
     for t in (0, 1):
         compare_tree(wl, t, got, dw.kw, name="copies")
     dw.close()
+
+
+# M, B, L, k, path-dependent correction: a step's list of at most 64 entries and of more, cut within a
+# family of siblings or not, ties below the root's children and one depth further
+SIBLINGS = [(4, 20, 2, 0, False), (4, 10, 2, 0, True), (4, 12, 2, 3, False), (16, 64, 2, 0, False),
+            (16, 41, 2, 0, True), (16, 64, 3, 0, True), (32, 64, 2, 0, False), (5, 64, 3, 0, True)]
+
+
+@pytest.mark.parametrize("scorer", [0, 2], ids=["cond", "static"])
+@pytest.mark.parametrize("c", SIBLINGS, ids=["-".join(map(str, c)) for c in SIBLINGS])
+def test_siblings_of_one_score(c, scorer):
+    """Siblings whose log-probs differ by 2^-20 below parents that score about -200 (an ulp of 2^-16):
+    their scores round together, and they leave in the order of their log-probs, which the correction
+    made another order than the slots'.  The oracle's (64-bit) scores are all apart: the same trees,
+    node for node."""
+    M, B, L, k, path = c
+    V, d_h = 4 * M, 64
+    wl = synth.random_small(M, batch=3, L=L, V=V, M=M, B=B, T=1.0, d_e=32, d_h=d_h, dtype=F, h0=path)
+    w, r = wl.weights, np.random.default_rng(B)
+    e = 2.0 ** -20
+    slot = np.arange(M)
+    w.emb[:], w.w_c[:], w.b_c[:] = 0.0, 0.0, 0.0
+    w.b_c[0] = 1.0
+    if path:   # (|w S| <= 64 2^-12 max |S|: slots' corrections of at most 32 2^-20 move by less than 2^-21,
+        # so log-probs stay two ulps apart or more: a chain's menus hold them rounded)
+        w.w_c[0] = 2.0 ** -12 * np.sign(r.standard_normal(d_h))
+    # the last depth's tokens: slots 2^-20 apart, the correction shuffles them
+    w.emb[V - M:, 0] = (slot + r.permutation(M)) * e
+    wl.logits[:] = -1000.0
+    for t in range(wl.batch):
+        for d in range(L - 1):   # well apart: one certain token, the others far below
+            wl.logits[t, d, d * M:(d + 1) * M] = np.where(slot == 0, 0.0, -200.0 - (1.0 + 6.1 * d) * slot - 0.01 * t)
+        wl.logits[t, L - 1, V - M:] = -slot * e
+    print(f"[grow] siblings {c} scorer {scorer}", flush=True)
+    dw = DeviceWorkload(wl, max_children=k, scorer=scorer)
+    got = dw.run()
+    dw.close()
+    turned = 0
+    for t in range(wl.batch):
+        ref = run_oracle(wl, t, **dw.kw)
+        n = ref["n_nodes"]
+        assert int(got["n_nodes"][t]) == n
+        gap = np.abs(np.diff(ref["scores"][:n]))   # (all but siblings well apart, or a certain child's: 0)
+        assert ((gap > 1e-3) | (gap == 0) | (np.diff(ref["parents"][:n]) == 0)).all()
+        for f in ("tokens", "parents", "depth", "mask"):
+            np.testing.assert_array_equal(got[f][t], ref[f], err_msg=f"tree {t} {f}")
+        s, p, tok = got["scores"][t], got["parents"][t], got["tokens"][t]
+        turned += int(np.sum((s[1:n] == s[:n - 1]) & (p[1:n] == p[:n - 1]) & (tok[1:n] < tok[:n - 1])))
+    assert turned >= 1   # (tokens ascend with the slot)
