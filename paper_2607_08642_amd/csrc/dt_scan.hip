@@ -332,7 +332,6 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
   const bool two = nbat > 1;
   load_batch<T, W>(ra, segr, 0);
   if (two) load_batch<T, W>(rb, segr, 1);
-  if (tid == 0) flag = 0;
 
   // ---- the first two batches' lower bound tb -----------------------------------
   const int bn0 = min(BATCH, seg_n);
@@ -366,6 +365,10 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
   float tb = wthr[0];
 #pragma unroll
   for (int i = 1; i < W; ++i) tb = fminf(tb, wthr[i]);
+  // (a bound of +inf -- ceil(M/W) lanes of every wave hold one -- lets nothing through
+  // that would show it: flagged here, the rest of the row's results unspecified.  The
+  // flag's other writers come after the barriers below.)
+  if (tid == 0) flag = tb == -NINF;
   const bool all_in = !(tb > NINF);
   const float tlow = all_in ? NINF : below(tb);
   // The tail's reference follows the bound, which every element the tail

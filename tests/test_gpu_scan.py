@@ -249,3 +249,20 @@ def test_scan_merge_of_many_segments(nlists, M):
     x[0, ::641] = 14.0
     x[1, 10200:10200 + min(300, V - 10200)] += 30.0
     _check(x, synth.DT_F32, M, 1.0, case=f"{nlists} lists M={M}")
+
+
+@pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("M", [1, 4, 64, 65, 256])
+def test_scan_many_infinities(M, dtype):
+    # rows of nothing but +inf, and rows that hold it often enough to make the first
+    # batches' bound +inf itself: flagged, in one segment and several, beside rows
+    # that are not
+    for V in (257, 4099, 10240, 20481, 5 * 10240 + 3):
+        x = synth.peaked_logits(13, 0, 6, V, synth.DT_F32, 1, 4, 6.0, 12.0).reshape(6, V)
+        x[1, :] = np.inf
+        x[2, ::3] = np.inf
+        x[3, :] = -np.inf
+        x[3, ::2] = np.inf
+        x[4, V // 2:] = np.inf
+        xd = synth.f32_to_bf16_bits(x) if dtype == synth.DT_BF16 else x
+        _check(xd, dtype, M, 0.7, case=f"infinities V={V} M={M}")

@@ -546,3 +546,15 @@ def test_repeatable_under_concurrent_load():
             np.testing.assert_array_equal(t0, tail2.cpu().numpy(), err_msg=f"scan rep {rep}")
     finally:
         dw.close()
+
+
+@pytest.mark.parametrize("scorer", [0, 1, 2], ids=["cond", "marg", "static"])
+@pytest.mark.parametrize("V,M", [(2000, 16), (2001, 64), (2001, 96), (30011, 64)])
+def test_rows_of_infinities(V, M, scorer):
+    # a tree with a row of +inf has no nodes and says so; its neighbours are built
+    wl = synth.random_small(V + M, batch=4, L=3, V=V, M=M, B=16, T=1.0, d_e=64, d_h=64)
+    wl.logits[1, 2, :] = np.inf
+    wl.logits[2, 0, ::2] = np.inf
+    _, got = run_case(wl, name=f"infinities V={V} M={M}", scorer=scorer)
+    for t in (1, 2):
+        assert int(got["status"][t]) == binding.DT_TREE_NONFINITE and int(got["n_nodes"][t]) == 0
