@@ -84,12 +84,12 @@ def test_adaptive_budget_small(case, scorer):
 
 
 def test_adaptive_budget_deep_qwen_shape():
-    # one tree per call: the 16-member production instance
+    # one tree per call: the register-list expansion, one workgroup per CU
     run_budget(synth.deep(), "deep", tol=TOL)
 
 
 def test_adaptive_budget_deep_concurrent_sampled():
-    # 32 trees per call: the 8-member production instance
+    # 32 trees per call: the register-list expansion, two workgroups per CU
     run_budget(synth.deep_concurrent(), "deep_concurrent", trees=[0, 3, 11, 20, 31], tol=TOL)
 
 

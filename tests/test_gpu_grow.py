@@ -132,6 +132,10 @@ SIBLINGS = [(4, 20, 2, 0, False), (4, 10, 2, 0, True), (4, 12, 2, 3, False), (16
 @pytest.mark.parametrize("scorer", [0, 2], ids=["cond", "static"])
 @pytest.mark.parametrize("c", SIBLINGS, ids=["-".join(map(str, c)) for c in SIBLINGS])
 def test_siblings_of_one_score(c, scorer):
+    check_siblings(c, scorer)
+
+
+def check_siblings(c, scorer):
     """Siblings whose log-probs differ by 2^-20 below parents that score about -200 (an ulp of 2^-16):
     their scores round together, and they leave in the order of their log-probs, which the correction
     made another order than the slots'.  The oracle's (64-bit) scores are all apart: the same trees,

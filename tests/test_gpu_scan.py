@@ -51,7 +51,7 @@ def test_scan_qwen_rows_bf16(T):
 
 @pytest.mark.parametrize("T", [0.05, 4.0])
 def test_scan_block_kernel_temperatures(T):
-    # rows of an odd length (4-byte loads: the block kernel), M above and below
+    # rows of an odd length (most begin off a 16-byte boundary), M above and below
     # 64, at a small temperature (exponents far below the row maximum) and a
     # large one
     x = synth.peaked_logits(3, 0, 8, 20001, synth.DT_F32, 1, 4, 6.0, 12.0)
@@ -136,9 +136,8 @@ def _mixed_rows(n_rows, V, seed):
 def test_scan_streaming_segments(dtype, V):
     # enough rows that every workgroup streams several batches of a segment
     # against its running lists (ramps and constant rows overflow the candidate
-    # regions; -inf blocks leave first batches without a finite bound).  Rows of
-    # 16-byte loads take the wave-streaming kernel at M <= 64, the others the
-    # block kernel.
+    # regions; -inf blocks leave first batches without a finite bound), with one
+    # list register per lane (M <= 64) and with four.
     x = _mixed_rows(1100, V, 21)
     if dtype == synth.DT_BF16:
         x = synth.f32_to_bf16_bits(x)
@@ -186,7 +185,7 @@ def test_scan_waves_without_enough_finite_lanes(dtype):
     # finite values only in the elements one wave of the first batch reads
     # (the first 300 of each 2048), so the other waves' bound inputs are -inf:
     # the segment's bound must then be -inf (every element a candidate), not
-    # that wave's; one- and two-batch segments, the wave and block kernels
+    # that wave's; one- and two-batch segments, rows on and off a 16-byte boundary
     rng = np.random.default_rng(9)
     for V in (10240, 20480, 10243):
         x = np.full((6, V), -np.inf, np.float32)

@@ -67,9 +67,9 @@ SWEEP = [
     (10, 2, 4, 64, 64, 20, 1.0, 32, 32, synth.DT_F32, {}, {}),
     (11, 1, 5, 333, 20, 30, 0.6, 36, 32, synth.DT_BF16, dict(max_children=8), {}),
     (12, 6, 16, 1500, 64, 64, 0.0, 64, 96, synth.DT_BF16, {}, dict(h0=True)),
-    # several segment lists per row (10240 logits each): the register tree
-    # merge with M < 64 and a 5-element last list, the one-wave merge of two
-    # lists, more than 16 lists (block merge) and M > 64 (block merges)
+    # several segment lists per row (10240 logits each): the tree merge with M < 64
+    # and a 5-element last list, two lists, more than 16 lists and M > 64 (the
+    # merge of any number of lists)
     (13, 1, 4, 30725, 48, 16, 0.8, 32, 32, synth.DT_F32, {}, {}),
     (14, 2, 3, 15000, 40, 12, 0.0, 32, 32, synth.DT_BF16, {}, {}),
     (15, 1, 4, 200000, 32, 16, 1.0, 32, 32, synth.DT_F32, {}, {}),
@@ -189,9 +189,9 @@ def test_budget_beyond_reachable_nodes(L, M, B):
 
 @pytest.mark.parametrize("batch,d_h", [(100, 64), (300, 32)])
 def test_many_trees_per_call(batch, d_h):
-    # more trees than XCD classes hold at once: 100 trees of two members each
-    # (13 per class, start-order member slots) and 300 one-member trees (more
-    # workgroups than CUs)
+    # more trees than XCD classes hold at once: 100 trees of two workgroups each
+    # (13 per class, start-order member slots) and 300 of one workgroup (more
+    # than CUs)
     wl = synth.random_small(81, batch=batch, L=4, V=300, M=8, B=10, T=0.8, d_e=32, d_h=d_h,
                             h0=True)
     run_case(wl, name=f"batch {batch}")
@@ -199,9 +199,9 @@ def test_many_trees_per_call(batch, d_h):
 
 @pytest.mark.parametrize("d_h,batch", [(160, 2), (768, 1), (1024, 1), (1024, 9)])
 def test_state_widths(d_h, batch):
-    # path-state widths off the tested grid: 160 (two members of 80 units), 768
-    # and 1024 (the largest), whose sixteen-member layouts exceed the LDS: eight
-    # members of 96 and 128 units
+    # path-state widths off the tested grid: 160 (five workgroups of 32 units), 768
+    # and 1024 (the largest; the general kernel), whose sixteen-member layouts exceed
+    # the LDS: eight members of 96 and 128 units
     wl = synth.random_small(91, batch=batch, L=5, V=600, M=16, B=14, T=0.8, d_e=64, d_h=d_h,
                             h0=True, w_scale=0.2)
     run_case(wl, name=f"d_h {d_h} batch {batch}")
@@ -224,8 +224,8 @@ def test_menus_of_the_whole_vocabulary():
 
 
 def test_odd_vocabulary_at_qwen_width():
-    # a vocabulary of 151937 bf16 logits (rows not 16-byte aligned: the block
-    # scan kernel, fifteen segment lists per row) at d_h = 512, M = 64
+    # a vocabulary of 151937 bf16 logits (rows not 16-byte aligned, fifteen segment
+    # lists per row) at d_h = 512, M = 64
     wl = synth.random_small(94, batch=1, L=4, V=151937, M=64, B=16, T=1.0, d_e=64, d_h=512,
                             dtype=synth.DT_BF16, w_scale=0.1)
     run_case(wl, name="odd V")
@@ -266,8 +266,8 @@ def test_concurrent_workload_sampled():
     run_case(qwen("concurrent"), trees=[0, 1, 7, 19, 31], name="concurrent", tol=QWEN_TOL)
 
 
-# ---- deep trees on the production instances (d_h = 512, M = 64, L = 16, bf16) ----
-# one tree per call runs the 16-member instance, 32 trees the 8-member one
+# ---- deep trees at d_h = 512, M = 64, L = 16, bf16 ----
+# one tree per call: one workgroup per CU; 32 trees: two
 
 @pytest.mark.parametrize("k", [0, 8, 2, 1])
 def test_deep_tree_at_qwen_shape(k):
@@ -304,8 +304,8 @@ def test_deep_concurrent_all_trees():
 
 
 def test_deep_qwen_shape_100_trees_sampled():
-    # 100 deep Qwen3-8B-shaped trees in one call: two members per tree on the
-    # generic instance (d_h 512 split in halves), 13 trees per XCD class
+    # 100 deep Qwen3-8B-shaped trees in one call: 32 groups of workgroups build them
+    # in turn
     wl = synth.deep_concurrent(batch=100)
     kinds, got = run_case(wl, trees=[0, 1, 49, 98, 99], name="deep x100", tol=QWEN_TOL)
     assert all(int(s) == 0 for s in got["status"][:100])
