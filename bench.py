@@ -26,7 +26,7 @@ workload.
 Prints ONE JSON line: trees/s for the whole job, the roofline of the dominant
 kernel (the expansion at one tree per call: fp32-precision MFMA work, priced
 against the fp32 peak; it is a chain of dependent steps, so the line's
-`latency` block carries us per dependent step and the occupancy), the scan's
+`latency` block carries us per dependent step and the steps per tree), the scan's
 HBM roofline, and the CPU baseline.
 
 --scorer marg|static times the ablation arms; --scorer head times
@@ -185,19 +185,23 @@ def head_on_expand(rank, G):
 
 
 def group_size(d_h, num_cus, batch):
-    """Workgroups per tree of the expansion kernel (the library's rule): the largest
-    power of two <= 16 with >= 32 hidden units (a multiple of 16) per member and
-    a grid of at most one workgroup per CU."""
+    """Workgroups per tree of the general expansion kernel, which builds the trees of
+    Domino's own head: the largest power of two <= 16 with >= 32 hidden units (a
+    multiple of 16) per member and a grid of at most one workgroup per CU."""
     G = 16
     while G > 1 and (d_h // G < 32 or (d_h // G) % 16 != 0 or 8 * G * ((batch + 7) // 8) > num_cus):
         G //= 2
     return G
 
 
-def register_list(w, M, B, scorer):
-    """Whether the call runs on the register-list expansion (the library's rule):
-    32 hidden units per workgroup of four waves, W_hh slices in registers."""
-    return (scorer == 0 and M <= 64 and B <= 64 and w.d_h <= (512 if w.dtype == 1 else 256))
+def tree_workgroups(w, scorer, head_group):
+    """Workgroups that build one tree of these workloads: head_group with Domino's own
+    head; else all of them (menus and budgets of at most 64, at most 16 scan segments
+    per row) run on the register-list expansion, 32 hidden units per workgroup, and
+    one workgroup where no state is needed."""
+    if scorer == "head":
+        return head_group
+    return 1 if scorer == "marg" else w.d_h // 32
 
 
 def main():
@@ -327,12 +331,6 @@ def main():
     num_cus = torch.cuda.get_device_properties(0).multi_processor_count
     G = group_size(w.d_h, num_cus, wl.batch)
     head_fast = head is not None and head_on_expand(HEAD_RANK, G)
-    grid, waves = (8 * G * ((wl.batch + 7) // 8)) if G > 1 else wl.batch, 8
-    if register_list(w, wl.M, wl.B, SCORERS[args.scorer]):
-        # at most two workgroups per CU: more trees than groups take turns
-        G, waves = w.d_h // 32, 4
-        groups = min(wl.batch, 8 * (2 * (num_cus // 8) // G))
-        grid = 8 * G * ((groups + 7) // 8)
     if head is None or head_fast:
         plan.set_profiling(1)
         for i in range(ncalls):
@@ -390,8 +388,7 @@ def main():
             "expanded_nodes_per_tree_mean": float(np.mean(exp_tree)),
             "alg_expansions_per_tree_mean": float(np.mean(alg_nodes)),
             "us_per_pop": exp_us / wl.B,   # per tree: the trees of a call run side by side
-            "workgroups_per_tree": G, "grid": grid,
-            "waves_per_workgroup": waves, "num_cus": num_cus,
+            "workgroups_per_tree": tree_workgroups(w, args.scorer, G), "num_cus": num_cus,
             "stats_calls": ncalls,
         })
     trees = wl.batch * args.steps
