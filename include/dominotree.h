@@ -43,12 +43,15 @@
  *
  * Envelope: 1 <= M <= min(V, 256); 1 <= B <= 256; 1 <= L <= 64;
  * 32 <= d_h <= 1024 with d_h % 32 == 0; 1 <= d_e <= 8192; 1 <= V < 2^31;
- * the per-row merge buffer, about 22 * ceil(V / 10240) * M + 20 * M bytes,
- * must fit 96 KiB (DT_ERR_UNSUPPORTED otherwise); the expansion kernel's LDS
- * layout must fit the device at some number of workgroups per tree (the plan
- * takes the largest that fits; on a 160 KiB device only d_h 864, 928 and 992
- * with M >= 128 fit at none).  Both are checked by dt_plan_create, the first
- * also by dt_scan_topm.
+ * V and M together are bounded by about 22 * ceil(V / 10240) * M + 20 * M <=
+ * 96 KiB (DT_ERR_UNSUPPORTED otherwise), a measure of a row's segment lists; the
+ * general expansion kernel's LDS layout, which sets that much aside, must fit the
+ * device at the workgroups per tree of every batch up to max_batch, whichever
+ * kernel a call takes (the plan takes the largest number that fits the batch and
+ * the LDS; on a 160 KiB device d_h 864, 928 and 992 with M > 128, d_h <= 64 with
+ * more than 4000 list entries per row, and d_h > 640 with wide menus or more than
+ * 64 trees per call can fit at none).  Both are checked by dt_plan_create, the
+ * first also by dt_scan_topm.
  */
 #ifndef DOMINOTREE_H
 #define DOMINOTREE_H

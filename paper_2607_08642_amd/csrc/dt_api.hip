@@ -255,9 +255,9 @@ static dt_status plan_init(dt_plan *p, int V, int d_e, int d_h, int wdt, int mod
     return fail(DT_ERR_SHAPE, "the model lives on device %d, the current device is %d", model_dev, dev);
   if (nxcd < 1 || nxcd > dt::kMaxXcd)
     return fail(DT_ERR_UNSUPPORTED, "device reports %d XCDs; 1 to %d are supported", nxcd, dt::kMaxXcd);
-  if (dt::merge_lds_bytes(dt::scan_geom(1, V, M)) > (size_t)dt::kMergeLdsMax)
-    return fail(DT_ERR_UNSUPPORTED, "the row merge of V and M needs %zu bytes of LDS, more than %d",
-                dt::merge_lds_bytes(dt::scan_geom(1, V, M)), dt::kMergeLdsMax);
+  if (dt::row_bound_bytes(dt::scan_geom(1, V, M)) > (size_t)dt::kRowBoundMax)
+    return fail(DT_ERR_UNSUPPORTED, "V and M are too large together (a row's lists: %zu bytes, at most %d)",
+                dt::row_bound_bytes(dt::scan_geom(1, V, M)), dt::kRowBoundMax);
   // the expansion's LDS at the group size of every batch in [1, max_batch]
   // (the group shrinks until its layout fits; only one member per tree can
   // still be too large)
@@ -680,8 +680,8 @@ dt_status dt_scan_workspace_size(int rows, int V, int M, size_t *bytes) {
   if (!bytes) return fail(DT_ERR_NULL, "bytes is required");
   if (rows < 1 || V < 1 || M < 1 || M > V) return fail(DT_ERR_SHAPE, "need rows, V >= 1 and 1 <= M <= V");
   if (M > dt::kMaxM) return fail(DT_ERR_UNSUPPORTED, "M must be <= 256");
-  if (dt::merge_lds_bytes(dt::scan_geom(rows, V, M)) > (size_t)dt::kMergeLdsMax)
-    return fail(DT_ERR_UNSUPPORTED, "V and M too large for the row merge");
+  if (dt::row_bound_bytes(dt::scan_geom(rows, V, M)) > (size_t)dt::kRowBoundMax)
+    return fail(DT_ERR_UNSUPPORTED, "V and M are too large together");
   *bytes = dt::scan_bytes(dt::scan_geom(rows, V, M));
   return DT_OK;
 }
@@ -696,8 +696,8 @@ dt_status dt_scan_topm(const void *logits, int rows, int V, int logits_dtype, in
   if (M > dt::kMaxM) return fail(DT_ERR_UNSUPPORTED, "M must be <= 256");
   if (!(T == T)) return fail(DT_ERR_SHAPE, "temperature is NaN");
   const dt::ScanGeom g = dt::scan_geom(rows, V, M);
-  if (dt::merge_lds_bytes(g) > (size_t)dt::kMergeLdsMax)
-    return fail(DT_ERR_UNSUPPORTED, "V and M too large for the row merge");
+  if (dt::row_bound_bytes(g) > (size_t)dt::kRowBoundMax)
+    return fail(DT_ERR_UNSUPPORTED, "V and M are too large together");
   const size_t need = dt::scan_bytes(g);
   if (!workspace || ws_bytes < need)
     return fail(DT_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, workspace ? ws_bytes : 0);

@@ -178,9 +178,10 @@ __host__ __device__ inline Lds lds_layout(int dh, int G, int M, int nchunks, int
   l.Sn = take(CH * UW * 4);
   l.ell = take(CH * MP * 4);
   l.rnk = take(CH * MP * 2);
-  // the row merges' LDS: NT keys per 64 slots of the menu
+  // the row merges' LDS: NT keys per 64 slots of the menu (and never less than the
+  // envelope's measure, so that the shapes it admits and their groups stay as they are)
   const int need = NT * 8 * (M > 128 ? 4 : (M > 64 ? 2 : 1));
-  const int sortb = sel::merge_buf_bytes(nchunks, M) > need ? sel::merge_buf_bytes(nchunks, M) : need;
+  const int sortb = sel::row_bound_bytes(nchunks, M) > need ? sel::row_bound_bytes(nchunks, M) : need;
   l.sortbuf = reuse;
   if (reuse + sortb > o) o = reuse + sortb;
   l.total = o;

@@ -25,11 +25,9 @@ constexpr int kScanThreads = 256;
 constexpr int kScanPerThread = 40;                         // elements held per thread
 constexpr int kScanChunk = kScanThreads * kScanPerThread;  // 10240
 constexpr int kScanSlots = 1024;    // scan workgroups resident at once (4 per CU of 256)
-constexpr int kMergeLdsMax = 96 * 1024;  // row merge buffer (sel::merge_buf_bytes) at most
+constexpr int kRowBoundMax = 96 * 1024;  // a row's segment lists (sel::row_bound_bytes) at most
 
-// fold GEMM tile (bf16 MFMA path)
-constexpr int kFoldBM = 128;
-constexpr int kFoldBN = 128;
+constexpr int kFoldBN = 128;  // columns of the fold GEMMs' widest tile: packed rows are a multiple
 
 // expansion kernel
 constexpr int kExpThreads = 512;
@@ -97,7 +95,7 @@ struct dt_model {
   float *b_hh;      // [3dh] fp32
   float *b_c;       // [d_e] fp32 (zeros when absent)
   int has_bc;
-  void *whh_t;      // W_hh in MFMA A-fragment order (see pack_whh_*_kernel)
+  void *whh_t;      // W_hh in MFMA A-fragment order (see pack_kernel)
   void *whh_rm;     // [3dh][dh] W_hh as given (weights dtype), for the Domino-head path
   int device;       // the device its memory lives on
   std::atomic<int> refs;  // the creator's reference plus one per plan
@@ -152,7 +150,7 @@ struct Workspace {
 };
 
 ScanGeom scan_geom(int rows, int V, int M);
-size_t merge_lds_bytes(const ScanGeom &g);  // LDS of the per-row merge (<= kMergeLdsMax)
+size_t row_bound_bytes(const ScanGeom &g);  // sel::row_bound_bytes (<= kRowBoundMax)
 size_t scan_bytes(const ScanGeom &g);
 // carve the scan part of a workspace; returns bytes used
 size_t carve_scan(char *base, const ScanGeom &g, Workspace *ws);

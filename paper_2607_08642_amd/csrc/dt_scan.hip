@@ -60,7 +60,7 @@ namespace {
 
 using sel::Tail;
 
-constexpr int kProjWaves = kScanThreads / 64;  // (launches with a projection: 256 threads)
+constexpr int W = kScanThreads / 64;  // waves of a workgroup
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -69,7 +69,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // row tile) with fp32 accumulation: the K = d_H columns split over the waves
 // in chunks of KC (one MFMA group: lane l holds KC/4 consecutive columns of
 // rank (tile row) l % 16 and of H row l % 16, at column group l / 16), the
-// wave partials summed in LDS (red: kProjWaves x 256 floats).  Out-of-range ranks,
+// wave partials summed in LDS (red: W x 256 floats).  Out-of-range ranks,
 // rows and columns read as zeros and are not stored.  bf16: 16x16x32 bf16
 // MFMAs on the stored values (exact products); fp32: 16x16x4 fp32 MFMAs.
 template <typename TW>
@@ -88,12 +88,12 @@ __device__ void head_proj_tile(const HeadProj &p, int rows, int tile, float *red
   using V = typename std::conditional<kBf, uint4, float4>::type;  // KL columns
   const int nch = (p.d_H + KC - 1) / KC;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int c0 = w; c0 < nch; c0 += kProjWaves * U) {
+  for (int c0 = w; c0 < nch; c0 += W * U) {
     V av[U], bv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int k = (c0 + u * kProjWaves) * KC + g * KL;  // (d_H % 8 == 0: a lane's KL are all in or out)
-      const bool ok = c0 + u * kProjWaves < nch && k < p.d_H;
+      const int k = (c0 + u * W) * KC + g * KL;  // (d_H % 8 == 0: a lane's KL are all in or out)
+      const bool ok = c0 + u * W < nch && k < p.d_H;
       av[u] = (ok && rok) ? *reinterpret_cast<const V *>(wr + k) : V{};
       bv[u] = (ok && qok) ? *reinterpret_cast<const V *>(hr + k) : V{};
     }
@@ -117,7 +117,7 @@ __device__ void head_proj_tile(const HeadProj &p, int rows, int tile, float *red
   static_assert(kScanThreads == 256, "one thread per tile element");
   const int e = threadIdx.x, el = e >> 2, ei = e & 3;
   float sum = red[e];
-  for (int v = 1; v < kProjWaves; ++v) sum += red[v * 256 + e];
+  for (int v = 1; v < W; ++v) sum += red[v * 256 + e];
   const int rr = rt * 16 + (el >> 4) * 4 + ei, qq = qt * 16 + (el & 15);
   if (rr < p.rank && qq < rows) p.a[(size_t)qq * p.rank + rr] = sum;
 }
@@ -170,7 +170,7 @@ struct Raw {
 // batch offset j*STEP + tid*EPL + e): straight-line 16-byte buffer loads; loads
 // past the segment's granules return zeros and cost no traffic, and pad_batch
 // makes what lies outside the row -inf.  Nothing waits for the data here.
-template <typename T, int W>
+template <typename T>
 __device__ inline void load_batch(Raw<T> &r, __amdgpu_buffer_rsrc_t seg, int b) {
   constexpr int EPL = Elem<T>::EPL;
   constexpr int STEP = W * 64 * EPL;
@@ -202,7 +202,7 @@ __device__ inline uint4 pad_granule(uint4 q, int lo, int hi) {
 }
 
 // the elements of a batch before `lo` and from `hi` on become -inf (lo < EPL)
-template <typename T, int W>
+template <typename T>
 __device__ inline void pad_batch(Raw<T> &r, int lo, int hi) {
   constexpr int EPL = Elem<T>::EPL;
   constexpr int STEP = W * 64 * EPL;
@@ -285,10 +285,10 @@ struct RowOut {
 // boundary; the last one takes what is left) of one row, plus the tail of the
 // rest.  Also clears `zero_n` ints at `zero_ptr` (barrier counters of the
 // expansion kernel that follows on the stream).
-// R: list registers per lane; W: waves; TWP: the weights dtype of a head
-// projection carried by the launch (void: none)
-template <typename T, int R, int W, typename TWP = void>
-__global__ __launch_bounds__(W * 64) void scan_kernel(
+// R: list registers per lane; TWP: the weights dtype of a head projection carried by
+// the launch (void: none)
+template <typename T, int R, typename TWP = void>
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const T *__restrict__ logits, ScanGeom g, float c, uint64_t *__restrict__ ckeys,
     float2 *__restrict__ ctail, int32_t *__restrict__ cflag, int32_t *__restrict__ zero_ptr,
     int zero_n, RowOut ro, HeadProj hp) {
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
   __shared__ float2 red[W];
   __shared__ int flag;
   if constexpr (!std::is_void<TWP>::value) {
-    static_assert(W == kProjWaves && W * kWaveRegion * 8 >= W * 256 * 4, "projection partials fit the regions");
+    static_assert(kWaveRegion * 8 >= 256 * 4, "projection partials fit the regions");
     if ((int)blockIdx.x >= g.nchunks) {
       head_proj_tile<TWP>(hp, g.rows, blockIdx.y * hp.extra + blockIdx.x - g.nchunks,
                           reinterpret_cast<float *>(regions));
@@ -330,12 +330,12 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
   asm volatile("" : "+v"(lb));
   Raw<T> ra, rb;
   const bool two = nbat > 1;
-  load_batch<T, W>(ra, segr, 0);
-  if (two) load_batch<T, W>(rb, segr, 1);
+  load_batch<T>(ra, segr, 0);
+  if (two) load_batch<T>(rb, segr, 1);
 
   // ---- the first two batches' lower bound tb -----------------------------------
   const int bn0 = min(BATCH, seg_n);
-  if (bn0 < BATCH || lo0 > 0) pad_batch<T, W>(ra, lo0, bn0);
+  if (bn0 < BATCH || lo0 > 0) pad_batch<T>(ra, lo0, bn0);
   float tmax = NINF;
 #pragma unroll
   for (int j = 0; j < NL; ++j)
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
     for (int e = 0; e < EPL; ++e) tmax = fmaxf(tmax, elem<T>(ra, j, e));
   if (two) {
     const int bn1 = min(BATCH, seg_n - BATCH);
-    if (bn1 < BATCH) pad_batch<T, W>(rb, 0, bn1);
+    if (bn1 < BATCH) pad_batch<T>(rb, 0, bn1);
 #pragma unroll
     for (int j = 0; j < NL; ++j)
 #pragma unroll
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
     const int bstart = b * BATCH;
     const int bn = min(BATCH, seg_n - bstart);
     const int lo = b == 0 ? lo0 : 0;
-    if (b > 0 && bn < BATCH) pad_batch<T, W>(raw, 0, bn);
+    if (b > 0 && bn < BATCH) pad_batch<T>(raw, 0, bn);
     // this batch's bound
     float te = tlow;
     if (b > 0) te = fmaxf(te, v_own);
@@ -488,10 +488,10 @@ __global__ __launch_bounds__(W * 64) void scan_kernel(
   // buffer measured slower: 43.2 against 40.0 us on 512 rows of 151936 bf16)
   for (int b = 0; b < nbat; b += 2) {
     process(ra, b);
-    if (b + 2 < nbat) load_batch<T, W>(ra, segr, b + 2);
+    if (b + 2 < nbat) load_batch<T>(ra, segr, b + 2);
     if (b + 1 < nbat) {
       process(rb, b + 1);
-      if (b + 3 < nbat) load_batch<T, W>(rb, segr, b + 3);
+      if (b + 3 < nbat) load_batch<T>(rb, segr, b + 3);
     }
   }
 
@@ -576,7 +576,7 @@ ScanGeom scan_geom(int rows, int V, int M) {
   return g;
 }
 
-size_t merge_lds_bytes(const ScanGeom &g) { return (size_t)sel::merge_buf_bytes(g.nchunks, g.M); }
+size_t row_bound_bytes(const ScanGeom &g) { return (size_t)sel::row_bound_bytes(g.nchunks, g.M); }
 
 size_t scan_bytes(const ScanGeom &g) {
   size_t b = 0;
@@ -621,11 +621,11 @@ static void launch_maybe_timed(F kernel, dim3 grid, dim3 block, uint32_t lds, hi
     hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
 }
 
-template <typename T, int R, int W, typename TWP>
+template <typename T, int R, typename TWP>
 static void launch_scan_k(const T *p, const ScanGeom &g, float c, const Workspace &ws, int32_t *zero_ptr,
                           int zero_n, const RowOut &ro, const HeadProj *hp, hipStream_t s, hipEvent_t t0,
                           hipEvent_t t1) {
-  launch_maybe_timed(scan_kernel<T, R, W, TWP>, dim3(g.nchunks + (hp ? hp->extra : 0), g.rows), dim3(W * 64), 0, s,
+  launch_maybe_timed(scan_kernel<T, R, TWP>, dim3(g.nchunks + (hp ? hp->extra : 0), g.rows), dim3(kScanThreads), 0, s,
                      t0, t1, p, g, c, ws.chunk_keys, ws.chunk_tail, ws.chunk_flag, zero_ptr, zero_n, ro,
                      hp ? *hp : HeadProj{});
 }
@@ -635,11 +635,11 @@ static void launch_scan_t(const T *p, const ScanGeom &g, float c, const Workspac
                           int zero_n, const RowOut &ro, const HeadProj *hp, hipStream_t s, hipEvent_t t0,
                           hipEvent_t t1) {
   if (hp && hp->wdt == DT_BF16)
-    launch_scan_k<T, R, 4, uint16_t>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
+    launch_scan_k<T, R, uint16_t>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
   else if (hp)
-    launch_scan_k<T, R, 4, float>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
+    launch_scan_k<T, R, float>(p, g, c, ws, zero_ptr, zero_n, ro, hp, s, t0, t1);
   else
-    launch_scan_k<T, R, 4, void>(p, g, c, ws, zero_ptr, zero_n, ro, nullptr, s, t0, t1);
+    launch_scan_k<T, R, void>(p, g, c, ws, zero_ptr, zero_n, ro, nullptr, s, t0, t1);
 }
 
 HeadProj head_proj_args(const dt_plan *p, int rows, const void *H, const dt_domino_head &hd, float *a_out) {

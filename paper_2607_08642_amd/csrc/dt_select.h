@@ -1,5 +1,5 @@
 // Device building blocks shared by the scan and the expansion kernels:
-// order-preserving keys, running log-sum-exp tails, bitonic sorts in LDS and
+// order-preserving keys, running log-sum-exp tails, bitonic sorts in registers and
 // the per-row merge of sorted chunk lists (Alg. 1 step 1; section 3.2).
 #pragma once
 
@@ -94,33 +94,6 @@ __device__ inline Tail block_tail(Tail t, float c, float2 *red) {
   return Tail{m, sum};
 }
 
-__host__ __device__ inline int pow2_at_least(int n, int lo) {
-  int p = lo;
-  while (p < n) p <<= 1;
-  return p;
-}
-
-// descending bitonic sort of buf[0..P), P a power of two; all NT threads call it
-template <int NT>
-__device__ void block_sort_desc(uint64_t *buf, int P) {
-  const int tid = threadIdx.x;
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int p = tid; p < P / 2; p += NT) {
-        const int i = 2 * p - (p & (j - 1));
-        const int ixj = i + j;
-        const uint64_t a = buf[i], b = buf[ixj];
-        const bool desc = (i & k) == 0;
-        if (desc ? (a < b) : (a > b)) {
-          buf[i] = b;
-          buf[ixj] = a;
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
 template <bool DEV_SCOPE, typename T>
 __device__ inline void put(T *p, T v) {
   if constexpr (DEV_SCOPE)
@@ -129,11 +102,12 @@ __device__ inline void put(T *p, T v) {
     *p = v;
 }
 
-// The envelope's bound on a row's segment lists: bytes per list entry and menu
-// slot (the public limit on V and M is stated in these terms; the expansion's LDS
-// layout reserves them).
+// The measure of a row's segment lists that the envelope bounds (kRowBoundMax), about
+// 22 bytes a list entry and 20 a menu slot, and that the general expansion's LDS
+// layout sets aside.  A contract on V and M: the merges themselves need 8 bytes a
+// thread for each 64 slots of the menu.
 __host__ __device__ inline int up16(int b) { return (b + 15) & ~15; }
-__host__ __device__ inline int merge_buf_bytes(int nlists, int M) {
+__host__ __device__ inline int row_bound_bytes(int nlists, int M) {
   const int n = nlists * M;
   const int q = (M + nlists - 1) / nlists;
   const int nhp = (nlists * q + 1) & ~1;
