@@ -42,10 +42,10 @@
 //    in depth order, so a depth's parents are the depth above), and the exchanged
 //    states of two steps.
 //
-// Measured per call (scan included) against the general kernel, us: one tree at
-// d_h = 512, M = 64, B = 16, L = 16: 30.2 / 37.4; long paths (9 steps) 62.1 / 85.6;
-// B = 64: 53.0 / 61.2; 32 trees 117.9 / 132.8; 100 trees of long paths 485 / 541;
-// d_h = 64, fp32: 29.4 / 48.5.  A step takes about 11,000 cycles (19,000 before):
+// Measured per call (scan included) against the general kernel, us, both in turn on
+// the same inputs: one tree at d_h = 512, M = 64, B = 16, L = 16: 31.4 / 37.9; long
+// paths (k = 8) 56.3 / 75.0; B = 64: 54.0 / 61.6; 32 trees 122 / 137; 100 trees of
+// long paths 500 / 540; d_h = 64, fp32: 29.6 / 48.9.  A step takes about 11,000 cycles (19,000 before):
 // exchange 2,600, ranking 1,600, children 1,400, products 1,200, selection 900,
 // GRU 850, correction 850, inputs 850, publishing 700.  Weights kept out of the
 // registers (spilled) or two kernels of 256 registers per SIMD for one tree were
@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
       const int total = n + nnew;
       uint32_t k = e_hi, p = e_lo | (uint32_t)lane;
       if (lane >= n) k = p = 0u;
-      bool tie = false;  // new siblings of one score, in slot order
+      uint64_t ties = 0;  // lanes whose entry is a new sibling of the next one, of one score
       if (total <= 64) {
         if (lane >= n && lane < total) {
           const uint64_t e = list[lane - n];
@@ -1112,7 +1112,8 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
           ks = push((int)k, at);
           if constexpr (ARM != kMarg) {
             const uint32_t ps = push((int)p, at), pn = pull((int)ps, lane + 1);
-            tie = lane + 1 < total && (uint32_t)pull((int)ks, lane + 1) == ks && (pn >> 19) == (ps >> 19) && (ps & 0x1000u);
+            ties = __ballot(lane + 1 < total && (uint32_t)pull((int)ks, lane + 1) == ks &&
+                            (pn >> 19) == (ps >> 19) && (ps & 0x1000u));
           }
         }
         p = push((int)p, at);
@@ -1142,12 +1143,12 @@ __global__ __launch_bounds__(GT, OCC) void grow_kernel(GrowArgs a) {
         p = (uint32_t)e;
         if constexpr (ARM != kMarg) {
           const uint64_t en = lane + 1 < B ? top[lane + 1] : *cut;
-          tie = lane < B && (e >> 19) == (en >> 19) && (p & 0x1000u);
+          ties = __ballot(lane < B && (e >> 19) == (en >> 19) && (p & 0x1000u));
         }
       }
       // (the root's children: score = log-prob, so slots order the equal ones; a
       // marginal menu's log-probs descend with the slot)
-      if (__builtin_expect(ARM != kMarg && d > 0 && __ballot(tie) != 0, 0)) {
+      if (__builtin_expect(ARM != kMarg && ties != 0 && d > 0, 0)) {
         // The children by their log-probs' order, formed from their values again.  The
         // partial corrections stay until every member has sent the next ones; the
         // ranks go where the nodes' states were, which nothing reads any more in this
