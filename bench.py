@@ -372,7 +372,7 @@ def main():
                 "achieved": exp_flops / (exp_us * 1e-6) / 1e12, "peak": FP32_PEAK_TFLOPS,
                 "unit": "TFLOP/s"}
     exp_roof["frac"] = exp_roof["achieved"] / exp_roof["peak"]
-    exp_roof["traffic"] = None if head is not None or args.max_children else \
+    exp_roof["traffic"] = None if args.scorer != "cond" or args.max_children else \
         traffic_from_profiles(wl.name, "expand")
     scan_gbps = scan_bytes / (scan_us * 1e-6) / 1e9
     scan_roof = {"kernel": "scan", "bound": "hbm", "achieved": scan_gbps, "peak": HBM_PEAK_GBS,

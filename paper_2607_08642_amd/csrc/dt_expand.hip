@@ -2032,6 +2032,8 @@ hipError_t launch_expand(const dt_plan *p, int batch, const float *h0, float inv
     fn = p->wdt == DT_BF16 ? (const void *)expand_kernel<uint16_t, 0, 0, 0, 0, true>
                            : (const void *)expand_kernel<float, 0, 0, 0, 0, true>;
   else if (a.W > 0) {
+    // (against the generic instance, W = 8, us a call: one tree 81.6 / 102.7, one deep
+    // tree 100.7 / 126.8, 32 trees 125.3 / 148.4)
     if (qwen && a.G == 16)
       fn = (const void *)expand_kernel<uint16_t, 512, 16, 64, 16, false, false, true>;
     else if (qwen && a.G == 8)

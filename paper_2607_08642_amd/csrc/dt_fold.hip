@@ -51,7 +51,8 @@ inline dim3 fold_grid(int ncol, int nrow, bool by_col) {
 // Bound by the LDS round trip of a K slice: the next slice's global loads are
 // issued before the current one is multiplied, so only LDS stands between two
 // slices.  151,936 rows at d_e = 4096, d_h = 512 (2.55 TFLOP): 6.9 ms with the
-// loads in line, 4.2 ms (610 TFLOP/s) ahead and with a row tile kept on one XCD.
+// loads in line, 4.1-4.3 ms (590-620 TFLOP/s) ahead and with a row tile kept on one
+// XCD.
 // cadd (nullable): c is also added to cadd[row].
 // ---------------------------------------------------------------------------
 template <int WR, int WC, int TI, int TJ, int BK>
