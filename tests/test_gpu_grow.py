@@ -135,24 +135,37 @@ def test_siblings_of_one_score(c, scorer):
     check_siblings(c, scorer)
 
 
-def check_siblings(c, scorer):
+@pytest.mark.parametrize("d_h,dt,batch", [(32, F, 3), (64, F, 3), (96, F, 3), (160, F, 3), (256, H, 3), (416, H, 3),
+                                          (512, H, 3), (512, H, 20)])
+def test_siblings_by_their_path(d_h, dt, batch):
+    """... where the path state decides their order: its parts from 1 to 16 workgroups, one and (the last)
+    two to a CU."""
+    check_siblings((16, 60 if batch < 20 else 30, 3, 0, "state"), 0, d_h, dt, batch)
+
+
+def check_siblings(c, scorer, d_h=64, dt=F, batch=3):
     """Siblings whose log-probs differ by 2^-20 below parents that score about -200 (an ulp of 2^-16):
     their scores round together, and they leave in the order of their log-probs, which the correction
     made another order than the slots'.  The oracle's (64-bit) scores are all apart: the same trees,
     node for node."""
     M, B, L, k, path = c
-    V, d_h = 4 * M, 64
-    wl = synth.random_small(M, batch=3, L=L, V=V, M=M, B=B, T=1.0, d_e=32, d_h=d_h, dtype=F, h0=path)
+    V = 4 * M
+    wl = synth.random_small(M, batch=batch, L=L, V=V, M=M, B=B, T=1.0, d_e=32, d_h=d_h, dtype=dt, logits_dtype=F,
+                            h0=bool(path), w_scale=4.0 / np.sqrt(d_h))
     w, r = wl.weights, np.random.default_rng(B)
     e = 2.0 ** -20
     slot = np.arange(M)
-    w.emb[:], w.w_c[:], w.b_c[:] = 0.0, 0.0, 0.0
-    w.b_c[0] = 1.0
-    if path:   # (|w S| <= 64 2^-12 max |S|: slots' corrections of at most 32 2^-20 move by less than 2^-21,
+    store = synth.f32_to_bf16_bits if dt == H else (lambda a: a)
+    emb, w_c, b_c = np.zeros((V, 32), np.float32), np.zeros((32, d_h), np.float32), np.zeros(32, np.float32)
+    b_c[0] = 0.0 if path == "state" else 1.0
+    if path == "state":   # (values, not log-probs, order siblings: they need not be ulps of a log-prob apart)
+        w_c[0] = 2.0 ** -2 * np.sign(r.standard_normal(d_h))
+    elif path:   # (|w S| <= 64 2^-12 max |S|: slots' corrections of at most 32 2^-20 move by less than 2^-21,
         # so log-probs stay two ulps apart or more: a chain's menus hold them rounded)
-        w.w_c[0] = 2.0 ** -12 * np.sign(r.standard_normal(d_h))
+        w_c[0] = 2.0 ** -12 * np.sign(r.standard_normal(d_h))
     # the last depth's tokens: slots 2^-20 apart, the correction shuffles them
-    w.emb[V - M:, 0] = (slot + r.permutation(M)) * e
+    emb[V - M:, 0] = (slot + r.permutation(M)) * e
+    w.emb, w.w_c, w.b_c = store(emb), store(w_c), store(b_c)
     wl.logits[:] = -1000.0
     for t in range(wl.batch):
         for d in range(L - 1):   # well apart: one certain token, the others far below
